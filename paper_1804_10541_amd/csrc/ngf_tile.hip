@@ -35,8 +35,8 @@
 // register windows (planes t, t-1, t-2) sit in fixed registers.
 //
 // P^T is a gather: each column accumulates its z contributions in registers;
-// when a node plane is complete the group reduces it over x and y in LDS and
-// writes the node block to its own slot of a partial buffer.  A node pass sums
+// when a node plane is complete the group reduces it over x and y on the matrix
+// cores and writes the node block to its own slot of a partial buffer.  A node pass sums
 // the slots that overlap each node in a fixed order, so results are
 // deterministic and no atomics are used.  Nothing per voxel reaches HBM.
 //
@@ -49,6 +49,8 @@
 #include "tile_common.h"
 
 namespace mfr {
+
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
 // LDS of one work-group of the voxel-tile kernel.
 template <int BX, int BY, int MODE, bool SSD>
@@ -67,9 +69,14 @@ struct TileSmem {
   // whose edge column is a ring column that writes 0) then adds exactly 0
   static constexpr int EP = (NEED_C && !SSD) ? BX : 0;
   float sE[NEED_C ? 2 : 1][4][NEED_C ? NX + 2 * EP : 1];
-  float sV[NEED_C ? 3 : 1][NEED_C ? NT : 1];
-  float sW[NEED_C ? 3 : 1][NEED_C ? BY * MAXNX : 1];
-  int sColLo[MAXNX], sColHi[MAXNX], sRowLo[MAXNY], sRowHi[MAXNY];
+  // a finished node plane of P^T, per column, waiting for its reduction over x and
+  // y; the pitch spreads the rows over the banks
+  static constexpr int VP = BX + 4;
+  float sV[NEED_C ? 3 : 1][NEED_C ? BY * VP : 1];
+  // conversion weights as the operands of that reduction: [node tile][step][lane]
+  static constexpr int XT = (MAXNX + 15) / 16, YT = (MAXNY + 15) / 16, RT = (BY + 15) / 16;
+  float sWx[NEED_C ? XT : 1][NEED_C ? BX / 4 : 1][NEED_C ? 64 : 1];
+  float sWy[NEED_C ? YT : 1][NEED_C ? 4 * RT : 1][NEED_C ? 64 : 1];
   Conv1 sCx[BX], sCy[BY];
   // z conversion and template-coordinate entries of planes zb-2 .. ze+1 (clamped
   // into the image): read at a uniform index every plane, from LDS rather than
@@ -85,20 +92,17 @@ __device__ __forceinline__ void tile_body(const TileParams& P, const int bid, co
                                           const float* __restrict__ pv, TileSmem<BX, BY, MODE, SSD>& S) {
   constexpr int NT = BX * BY;
   constexpr int TX = BX - 2, TY = BY - 2;   // own columns per tile
-  constexpr int MAXNX = BX + 1;
   constexpr bool HV = (MODE == MODE_HV);
   constexpr bool NEED_C = (MODE != MODE_OBJ);
   auto& sTw = S.sTw;
   auto& sR = S.sR;
   auto& sA = S.sA;
   auto& sE = S.sE;
-  constexpr int EP = TileSmem<BX, BY, MODE, SSD>::EP;
+  using Sm = TileSmem<BX, BY, MODE, SSD>;
+  constexpr int EP = Sm::EP, VP = Sm::VP;
   auto& sV = S.sV;
-  auto& sW = S.sW;
-  auto& sColLo = S.sColLo;
-  auto& sColHi = S.sColHi;
-  auto& sRowLo = S.sRowLo;
-  auto& sRowHi = S.sRowHi;
+  auto& sWx = S.sWx;
+  auto& sWy = S.sWy;
   auto& sCx = S.sCx;
   auto& sCy = S.sCy;
   auto& sCz = S.sCz;
@@ -173,26 +177,14 @@ __device__ __forceinline__ void tile_body(const TileParams& P, const int bid, co
     if (tid < BX) sCx[tid] = P.cx[min(max(x0 - 1 + tid, 0), P.mx - 1)];
     if (tid < BY) sCy[tid] = P.cy[min(max(y0 - 1 + tid, 0), P.my - 1)];
     __syncthreads();
-    for (int w = tid; w < nxl + nyl; w += NT) {
-      const bool isx = w < nxl;
-      const int i = isx ? w : w - nxl;
-      const int ng = (isx ? nox : noy) + i;
-      const int la = isx ? lxa : lya, lb = isx ? lxb : lyb;
-      int lo = lb + 1, hi = -1;
-      for (int l = la; l <= lb; ++l) {
-        const int n0 = isx ? sCx[l].n0 : sCy[l].n0;
-        if (n0 == ng || n0 + 1 == ng) {
-          lo = min(lo, l);
-          hi = max(hi, l);
-        }
-      }
-      if (isx) {
-        sColLo[i] = lo;
-        sColHi[i] = hi;
-      } else {
-        sRowLo[i] = lo;
-        sRowHi[i] = hi;
-      }
+    for (int w = tid; w < ((nxl + 15) / 16) * (BX / 4) * 64; w += NT) {
+      const int c16 = w & 15, l = (w >> 4) % BX, nt = w / (16 * BX);   // lane (l & 3, c16) of step l / 4
+      sWx[nt][l >> 2][w & 63] = conv_weight(sCx[l], nox + 16 * nt + c16);
+    }
+    for (int w = tid; w < ((nyl + 15) / 16) * Sm::RT * 256; w += NT) {
+      const int lane = w & 63, r = (w >> 6) % (4 * Sm::RT), mt = w / (256 * Sm::RT);
+      const int row = (r >> 2) * 16 + 4 * (lane >> 4) + (r & 3);
+      sWy[mt][r][lane] = row < BY ? conv_weight(sCy[min(row, BY - 1)], noy + 16 * mt + (lane & 15)) : 0.f;
     }
   }
 
@@ -201,52 +193,115 @@ __device__ __forceinline__ void tile_body(const TileParams& P, const int bid, co
   const int pslot = ((chunk % P.smz) * P.smy + tile_y % P.smy) * P.smx + tile_x % P.smx;
   float* const part = P.part + (size_t)pslot * 3 * (size_t)P.nbar;
 
-  // Writes one node plane (local index kloc) of the transposed conversion:
-  // reduce the per-column sums acc over x, then y, into the slot's node block.
-  const int nrow = lyb - lya + 1;
+  // Reduction of component d of the node plane in sV (local index kloc) over x,
+  // then y, for the 16 node columns from 16 nt on, by one wave: two products with
+  // the conversion weights on the matrix cores (v_mfma_f32_16x16x4: float32
+  // products and sums).  The first leaves D[row][node x] with row 4 quad + r in
+  // register r, which is what the second takes as its operand for the rows 4 quad
+  // + r, so nothing goes through LDS in between: 12 matrix instructions per
+  // component for up to 16 x 16 nodes.
+  auto reduce = [&](int kloc, int d, int nt) {
+    if constexpr (NEED_C) {
+      constexpr int RT = Sm::RT, KS = BX / 4;
+      // (opaque here, so that nothing of the reduction is kept in registers over the march)
+      int lane = tid & 63;
+      asm volatile("" : "+v"(lane));
+      const int c16 = lane & 15, quad = lane >> 4;
+      const float* const V = &sV[d][0];
+      const size_t o0 = (size_t)d * P.nbar + (size_t)(noz + kloc) * nxy + (size_t)noy * P.nx + nox;
+      f32x4 acc[RT];
+      float fin = 0.f;   // stays 0 if every column's value is finite, else turns NaN
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) {
+        const float* const row = V + min(rt * 16 + c16, BY - 1) * VP + quad;
+        f32x4 s0 = (f32x4){0.f, 0.f, 0.f, 0.f}, s1 = s0;   // two chains: half the latency
+#pragma unroll
+        for (int i = 0; i < KS; i += 8) {
+          float a[8], b[8];
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            a[j] = row[4 * (i + j)];
+            b[j] = sWx[nt][i + j][lane];
+          }
+#pragma unroll
+          for (int j = 0; j < 8; j += 2) {
+            s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], b[j], s0, 0, 0, 0);
+            s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j + 1], b[j + 1], s1, 0, 0, 0);
+          }
+#pragma unroll
+          for (int j = 0; j < 8; ++j) fin = fmaf(a[j], 0.f, fin);
+        }
+        acc[rt] = s0 + s1;
+      }
+      // a zero weight must not carry an infinity or NaN of a far column to a node:
+      // such a plane is summed without the matrix cores, zero weights left out
+      const bool bad = __any(fin != 0.f);
+      if (bad) {
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+          acc[rt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma clang loop unroll(disable)
+          for (int l = 0; l < BX; ++l) {
+            const float w = sWx[nt][l >> 2][16 * (l & 3) + c16];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const float v = V[min(rt * 16 + 4 * quad + r, BY - 1) * VP + l];
+              acc[rt][r] = w != 0.f ? fmaf(w, v, acc[rt][r]) : acc[rt][r];
+            }
+          }
+        }
+      }
+#pragma clang loop unroll(disable)
+      for (int mt = 0; mt * 16 < nyl; ++mt) {
+        f32x4 o = (f32x4){0.f, 0.f, 0.f, 0.f};
+        if (bad) {
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt)
+#pragma clang loop unroll(disable)
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+              for (int r = 0; r < 4; ++r) {
+                const float v = __shfl(acc[rt][r], 16 * q + c16, 64);   // row 16 rt + 4 q + r
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                  const float w = sWy[mt][4 * rt + r][16 * q + 4 * quad + k];
+                  o[k] = w != 0.f ? fmaf(w, v, o[k]) : o[k];
+                }
+              }
+        } else {
+          f32x4 o1 = (f32x4){0.f, 0.f, 0.f, 0.f};
+          float a[4 * RT];
+#pragma unroll
+          for (int r = 0; r < 4 * RT; ++r) a[r] = sWy[mt][r][lane];
+#pragma unroll
+          for (int r = 0; r < 4 * RT; r += 2) {
+            o = __builtin_amdgcn_mfma_f32_16x16x4f32(a[r], acc[r >> 2][r & 3], o, 0, 0, 0);
+            o1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[r + 1], acc[r >> 2][(r & 3) + 1], o1, 0, 0, 0);
+          }
+          o += o1;
+        }
+        if (16 * nt + c16 < nxl) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int fr = 16 * mt + 4 * quad + r;
+            if (fr < nyl) part[o0 + (size_t)fr * P.nx + 16 * nt + c16] = o[r];
+          }
+        }
+      }
+    }
+  };
+  // Writes one node plane (local index kloc) of the transposed conversion: the
+  // per-column sums go to LDS and, behind one barrier, one wave per component and 16
+  // node columns reduces them; the others go on.  sV is written again only behind a
+  // later barrier.
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), tasks = 3 * ((nxl + 15) / 16);
   auto flush = [&](const float (&acc)[3], int kloc) {
     if constexpr (NEED_C) {   // (only the derivative modes gather)
-      if (inC) {
-        sV[0][tid] = acc[0];
-        sV[1][tid] = acc[1];
-        sV[2][tid] = acc[2];
-      }
+#pragma unroll
+      for (int d = 0; d < 3; ++d) sV[d][ty * VP + tx] = inC ? acc[d] : 0.f;
       __syncthreads();
-      for (int w = tid; w < nxl * nrow; w += NT) {   // x reduction: node column fj, local row ly
-        const int fj = w % nxl, ly = lya + w / nxl;
-        const int jg = nox + fj;
-        float s0 = 0.f, s1 = 0.f, s2 = 0.f;
-        for (int l = sColLo[fj]; l <= sColHi[fj]; ++l) {
-          const Conv1 c = sCx[l];
-          const float wt = (c.n0 == jg) ? 1.0f - c.f : c.f;
-          const int q = ly * BX + l;
-          s0 = fmaf(wt, sV[0][q], s0);
-          s1 = fmaf(wt, sV[1][q], s1);
-          s2 = fmaf(wt, sV[2][q], s2);
-        }
-        sW[0][ly * MAXNX + fj] = s0;
-        sW[1][ly * MAXNX + fj] = s1;
-        sW[2][ly * MAXNX + fj] = s2;
-      }
-      __syncthreads();
-      for (int w = tid; w < nxl * nyl; w += NT) {   // y reduction: node (fj, fr)
-        const int fj = w % nxl, fr = w / nxl;
-        const int ig = noy + fr;
-        float s0 = 0.f, s1 = 0.f, s2 = 0.f;
-        for (int l = sRowLo[fr]; l <= sRowHi[fr]; ++l) {
-          const Conv1 c = sCy[l];
-          const float wt = (c.n0 == ig) ? 1.0f - c.f : c.f;
-          const int q = l * MAXNX + fj;
-          s0 = fmaf(wt, sW[0][q], s0);
-          s1 = fmaf(wt, sW[1][q], s1);
-          s2 = fmaf(wt, sW[2][q], s2);
-        }
-        const size_t o = ((size_t)(noz + kloc) * P.ny + (noy + fr)) * P.nx + (nox + fj);
-        part[o] = s0;
-        part[o + (size_t)P.nbar] = s1;
-        part[o + 2 * (size_t)P.nbar] = s2;
-      }
-      __syncthreads();
+      for (int w = wave; w < tasks; w += NT / 64) reduce(kloc, w % 3, w / 3);
+      if constexpr (SSD) __syncthreads();
     }
   };
 
@@ -480,6 +535,7 @@ __device__ __forceinline__ void tile_body(const TileParams& P, const int bid, co
 
   if constexpr (NEED_C) {
     flush(acc_lo, KL - noz);
+    __syncthreads();
     flush(acc_hi, KL + 1 - noz);
   }
   if constexpr (MODE != MODE_HV) block_sum_store<NT>(obj, P.red + bid, sRed);
