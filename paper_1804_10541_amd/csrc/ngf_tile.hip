@@ -202,7 +202,7 @@ __device__ __forceinline__ void tile_body(const TileParams& P, const int bid, co
   // component for up to 16 x 16 nodes.
   auto reduce = [&](int kloc, int d, int nt) {
     if constexpr (NEED_C) {
-      constexpr int RT = Sm::RT, KS = BX / 4;
+      constexpr int RT = Sm::RT, KS = BX / 4, G = RT > 1 ? 4 : 8;   // row tiles, steps, steps per load group
       // (opaque here, so that nothing of the reduction is kept in registers over the march)
       int lane = tid & 63;
       asm volatile("" : "+v"(lane));
@@ -216,20 +216,21 @@ __device__ __forceinline__ void tile_body(const TileParams& P, const int bid, co
         const float* const row = V + min(rt * 16 + c16, BY - 1) * VP + quad;
         f32x4 s0 = (f32x4){0.f, 0.f, 0.f, 0.f}, s1 = s0;   // two chains: half the latency
 #pragma unroll
-        for (int i = 0; i < KS; i += 8) {
-          float a[8], b[8];
+        for (int i = 0; i < KS; i += G) {
+          if constexpr (RT > 1) __builtin_amdgcn_sched_barrier(0);   // (registers)
+          float a[G], b[G];
 #pragma unroll
-          for (int j = 0; j < 8; ++j) {
+          for (int j = 0; j < G; ++j) {
             a[j] = row[4 * (i + j)];
             b[j] = sWx[nt][i + j][lane];
           }
 #pragma unroll
-          for (int j = 0; j < 8; j += 2) {
+          for (int j = 0; j < G; j += 2) {
             s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], b[j], s0, 0, 0, 0);
             s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j + 1], b[j + 1], s1, 0, 0, 0);
           }
 #pragma unroll
-          for (int j = 0; j < 8; ++j) fin = fmaf(a[j], 0.f, fin);
+          for (int j = 0; j < G; ++j) fin = fmaf(a[j], 0.f, fin);
         }
         acc[rt] = s0 + s1;
       }
