@@ -107,7 +107,9 @@ const char* mfr_last_error(void);
 
 /* Bytes of device workspace a context for `grid` needs (tile partial sums,
  * reduction partials, lookup tables, the template copy with a zero border
- * that realises its Dirichlet extension, and the six node vectors of PCG). */
+ * that realises its Dirichlet extension, and the six node vectors of PCG).
+ * Where a smaller workspace holds the same problem split into fewer, longer
+ * chunks, a context accepts it as well and runs slower. */
 mfr_status mfr_workspace_size(const mfr_grid* grid, size_t* bytes);
 
 /* Create a context bound to `hip_stream` (a hipStream_t; NULL = default
@@ -511,9 +513,9 @@ mfr_status mfr_cnn_conv_bwd_weight(int32_t nx, int32_t ny, int32_t nz, const uin
 
 /* ---- Tile configuration ---------------------------------------------------------
  * Shape of the voxel-tile work-groups (bx x by threads: 32x16, 64x8, 32x32 or
- * 64x16), the number of z planes per group (chunk_len; 0 = derived from
- * target_groups) and the number of work-groups the derived split aims for
- * (target_groups; 0 = 2048), for contexts and batches created afterwards in
+ * 64x16), the number of z planes per group (chunk_len; 0 = derived) and the
+ * number of work-groups the derived split aims for (target_groups; 0 = chosen
+ * from the grid by an estimate of the rounds of work-groups), for contexts and batches created afterwards in
  * this process.  Returns MFR_EINVAL for an unsupported shape or a negative
  * count.  The tile autotuner sets it from measured timings. */
 typedef struct {

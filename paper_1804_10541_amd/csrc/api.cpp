@@ -221,6 +221,43 @@ static int most_chunks(const std::vector<Conv1>& c, int n, int len) {
   return most;
 }
 
+// Chunks of a march over `planes` planes by xy column blocks, each chunk costing
+// its planes plus `lead` planes of lead-in: the number of chunks (of min_len to
+// kMaxChunk planes) with the least estimated time on 256 CUs.  A CU holds per_cu
+// groups at once; where it holds a single one of two, that one advances
+// faster, by solo.  Rounds of 256 per_cu groups follow each other; a last round
+// of at most one group per CU costs solo of a full one.  Measured with the
+// Hessian product (32 x 16 columns, two groups per CU, solo 0.7, lead-in 4): 6
+// chunks instead of 4 at 512x512x900 1959 -> 1847 us, 10 of 10 planes instead of 6
+// of 16 at 128x128x96 49 -> 38 us, 8 of 4 instead of 2 of 16 at 32^3 35 -> 17 us
+// (short chunks leave fewer planes to march one after the other; where the chip
+// is full they only add lead-in planes).
+static int pick_chunks(long long xy, int planes, int min_len, int per_cu, double lead, double solo) {
+  const long long slots = 256LL * per_cu;
+  int best = 1;
+  double best_t = 0.0;
+  for (int c = (planes + kMaxChunk - 1) / kMaxChunk; c <= std::max(1, planes / min_len); ++c) {
+    const int len = (planes + c - 1) / c;
+    const long long groups = xy * ((planes + len - 1) / len);
+    const long long full = groups / slots, rem = groups % slots;
+    const double rounds = (double)full + (rem == 0 ? 0.0 : rem <= 256 && per_cu > 1 ? solo : 1.0);
+    const double t = rounds * (len + lead);
+    if (best_t == 0.0 || t < 0.99 * best_t) {   // (ties: fewer, longer chunks)
+      best_t = t;
+      best = c;
+    }
+  }
+  return best;
+}
+
+// The least chunk length, from 4 planes on, with at most two chunks holding one
+// node plane, so that the partial slots of P^T along the march stay at two.
+static int min_chunk(const std::vector<Conv1>& c, int n) {
+  int len = 4;
+  while (len < (int)c.size() && most_chunks(c, n, len) > 2) ++len;
+  return len;
+}
+
 static Tiling make_tiling_plane(const Geo& g, const std::vector<Conv1>& cx, const std::vector<Conv1>& cy) {
   Tiling t;
   const mfr_tile_config cfg = current_tile_config();
@@ -268,7 +305,7 @@ static Tiling make_tiling_plane(const Geo& g, const std::vector<Conv1>& cx, cons
 }
 
 Tiling make_tiling(const Geo& g, const std::vector<Conv1>& cx, const std::vector<Conv1>& cy,
-                   const std::vector<Conv1>& cz) {
+                   const std::vector<Conv1>& cz, bool compact) {
   if (g.dim == 2) return make_tiling_plane(g, cx, cy);
   Tiling t;
   const mfr_tile_config cfg = current_tile_config();
@@ -277,9 +314,14 @@ Tiling make_tiling(const Geo& g, const std::vector<Conv1>& cx, const std::vector
   t.tiles_x = (g.m[0] + TX - 1) / TX;
   t.tiles_y = (g.m[1] + TY - 1) / TY;
   const int xy = t.tiles_x * t.tiles_y;
-  const int target = cfg.target_groups > 0 ? cfg.target_groups : 2048;
-  int chunks = std::max(1, (target + xy - 1) / xy);
-  chunks = std::min(chunks, std::max(1, g.m[2] / 16));
+  const int minc = min_chunk(cz, g.n[2]);
+  int chunks;
+  if (cfg.target_groups > 0 || compact) {   // a given number of groups, chunks of at least 16 planes
+    const int target = cfg.target_groups > 0 ? cfg.target_groups : 2048;
+    chunks = std::min(std::max(1, (target + xy - 1) / xy), std::max(1, g.m[2] / 16));
+  } else {
+    chunks = pick_chunks(xy, g.m[2], minc, t.shape.bx * t.shape.by > 512 ? 1 : 2, 4.0, 0.7);
+  }
   int clen = (g.m[2] + chunks - 1) / chunks;
   if (cfg.chunk_len > 0) clen = cfg.chunk_len;
   t.chunk_len = std::min(std::min(clen, g.m[2]), kMaxChunk);
@@ -301,14 +343,16 @@ Tiling make_tiling(const Geo& g, const std::vector<Conv1>& cx, const std::vector
   t.smx = most_groups(cx, g.n[0], TX, t.tiles_x);
   t.smy = most_groups(cy, g.n[1], TY, t.tiles_y);
   t.smz = most_chunks(cz, g.n[2], t.chunk_len);
-  // the diagonal's own tiling: 2048 groups (two per CU resident, eight rounds);
-  // a group's z node block spans the planes its rows' z stencils reach
+  // the diagonal's own tiling (two groups per CU, two planes of lead-in and one
+  // node plane more to write): its march is bound by instruction issue sooner, so
+  // a single group on a CU gains less (solo 0.8); a group's z node block spans the planes its rows' z stencils reach
   DiagTiling& d = t.dg;
   const int DX = kDiagBX - 2, DY = kDiagBY - 2;
   d.tiles_x = (g.m[0] + DX - 1) / DX;
   d.tiles_y = (g.m[1] + DY - 1) / DY;
   const int dxy = d.tiles_x * d.tiles_y;
-  int dch = std::min(std::max(1, (4096 + dxy - 1) / dxy), std::max(1, g.m[2] / 16));
+  const int dch = compact ? std::min(std::max(1, (4096 + dxy - 1) / dxy), std::max(1, g.m[2] / 16))
+                          : pick_chunks(dxy, g.m[2], minc, 2, 3.0, 0.8);
   d.chunk_len = std::min(std::min((g.m[2] + dch - 1) / dch, g.m[2]), kMaxChunk);
   d.chunks = (g.m[2] + d.chunk_len - 1) / d.chunk_len;
   d.nxt = d.nyt = d.nzt = 0;
@@ -616,6 +660,10 @@ mfr_status ctx_init(mfr_ctx* c, const mfr_grid* grid, void* stream, void* ws, si
   c->tiling = make_tiling(g, cx, cy, cz);
   if (!valid_shape(c->tiling.shape)) return fail(MFR_EINVAL, "unsupported tile shape %dx%d", c->tiling.shape.bx, c->tiling.shape.by);
   c->lay = make_layout(g, c->tiling);
+  if (ws_bytes < c->lay.total) {   // the longer chunks of the compact tiling need fewer partial blocks
+    c->tiling = make_tiling(g, cx, cy, cz, true);
+    c->lay = make_layout(g, c->tiling);
+  }
   if (!ws) return fail(MFR_EINVAL, "workspace is NULL");
   if (reinterpret_cast<uintptr_t>(ws) % 256 != 0) return fail(MFR_EINVAL, "workspace must be 256-byte aligned");
   if (ws_bytes < c->lay.total)
@@ -871,6 +919,31 @@ mfr_status ctx_init(mfr_ctx* c, const mfr_grid* grid, void* stream, void* ws, si
   c->red_node = q.red;
   for (int k = 0; k < 8; ++k) c->vec[k] = at<float>(c->ws, L.vec) + (size_t)k * 3 * g.nbar;
   c->vec_blocks = (int)std::min<size_t>((3 * g.nbar + kVecBlock - 1) / kVecBlock, 1024);
+  return MFR_OK;
+}
+
+mfr_status ctx_workspace(const mfr_grid* grid, bool compact, size_t* bytes) {
+  Geo g;
+  MFR_TRY(make_geo(grid, &g));
+  if (!bytes) return fail(MFR_EINVAL, "bytes is NULL");
+  auto cx = conv_table(g.m[0], g.n[0]);
+  auto cy = conv_table(g.m[1], g.n[1]);
+  auto cz = conv_table(g.m[2], g.n[2]);
+  auto total = [&](bool small, size_t* out) -> mfr_status {
+    const Tiling t = make_tiling(g, cx, cy, cz, small);
+    if (g.dim == 3 && !valid_shape(t.shape))
+      return fail(MFR_EINVAL, "unsupported tile shape %dx%d", t.shape.bx, t.shape.by);
+    *out = make_layout(g, t).total;
+    return MFR_OK;
+  };
+  size_t n = 0;
+  MFR_TRY(total(false, &n));
+  if (compact) {
+    size_t k = 0;
+    MFR_TRY(total(true, &k));
+    n = std::min(n, k);
+  }
+  *bytes = n;
   return MFR_OK;
 }
 
@@ -1231,18 +1304,7 @@ int mfr_abi_version(void) { return MFR_ABI_VERSION; }
 
 const char* mfr_last_error(void) { return g_err.c_str(); }
 
-mfr_status mfr_workspace_size(const mfr_grid* grid, size_t* bytes) {
-  Geo g;
-  MFR_TRY(make_geo(grid, &g));
-  if (!bytes) return fail(MFR_EINVAL, "bytes is NULL");
-  auto cx = conv_table(g.m[0], g.n[0]);
-  auto cy = conv_table(g.m[1], g.n[1]);
-  auto cz = conv_table(g.m[2], g.n[2]);
-  Tiling t = make_tiling(g, cx, cy, cz);
-  if (g.dim == 3 && !valid_shape(t.shape)) return fail(MFR_EINVAL, "unsupported tile shape %dx%d", t.shape.bx, t.shape.by);
-  *bytes = make_layout(g, t).total;
-  return MFR_OK;
-}
+mfr_status mfr_workspace_size(const mfr_grid* grid, size_t* bytes) { return ctx_workspace(grid, false, bytes); }
 
 mfr_status mfr_create(const mfr_grid* grid, void* hip_stream, void* workspace, size_t ws_bytes, mfr_ctx** out) {
   if (!out) return fail(MFR_EINVAL, "out is NULL");
@@ -1488,7 +1550,7 @@ mfr_status mfr_pcg_solve_async(mfr_ctx* c, const float* u, const float* b, float
 namespace mfr {
 
 
-mfr_status ml_levels(const mfr_grid* finest, int levels, std::vector<Level>* out, size_t* total) {
+mfr_status ml_levels(const mfr_grid* finest, int levels, std::vector<Level>* out, size_t* total, bool compact) {
   if (levels < 1 || levels > 8) return fail(MFR_EINVAL, "levels must be in 1..8");
   std::vector<Level> L(levels);
   L[levels - 1].grid = *finest;
@@ -1526,7 +1588,7 @@ mfr_status ml_levels(const mfr_grid* finest, int levels, std::vector<Level>* out
   size_t ctx_ws = 0;
   for (int l = 0; l < levels; ++l) {
     size_t b = 0;
-    MFR_TRY(mfr_workspace_size(&L[l].grid, &b));
+    MFR_TRY(ctx_workspace(&L[l].grid, compact, &b));
     ctx_ws = std::max(ctx_ws, b);
   }
   o = align_up(ctx_ws);
@@ -1575,6 +1637,8 @@ mfr_status mfr_register_multilevel(const mfr_grid* finest, const mfr_ml_opts* o,
   std::vector<Level> L;
   size_t need = 0;
   MFR_TRY(ml_levels(finest, o->levels, &L, &need));
+  const bool compact = ws_bytes < need;
+  if (compact) MFR_TRY(ml_levels(finest, o->levels, &L, &need, true));
   if (ws_bytes < need) return fail(MFR_ENOMEM, "workspace of %zu bytes is smaller than the required %zu", ws_bytes, need);
   const int nl = o->levels;
   if (o->precond == 2) MFR_TRY(pc_check_grid(o->pc, L[nl - 1].geo));   // before any level runs
@@ -1595,7 +1659,7 @@ mfr_status mfr_register_multilevel(const mfr_grid* finest, const mfr_ml_opts* o,
   size_t ctx_ws = 0;
   for (int l = 0; l < nl; ++l) {
     size_t b = 0;
-    MFR_TRY(mfr_workspace_size(&L[l].grid, &b));
+    MFR_TRY(ctx_workspace(&L[l].grid, compact, &b));
     ctx_ws = std::max(ctx_ws, b);
   }
   const size_t off_ptab = align_up(L[nl - 1].off_u + sizeof(float) * gf.nc() * gf.nbar);

@@ -45,7 +45,7 @@ namespace {
 
 constexpr int kGraphIters = 8;   // CG iterations per captured graph
 
-mfr_status batch_layout(int n, const mfr_grid* grids, int levels, mfr_batch* b, size_t* total) {
+mfr_status batch_layout(int n, const mfr_grid* grids, int levels, mfr_batch* b, size_t* total, bool compact = false) {
   if (n < 1 || n > kMaxBatch) return fail(MFR_EINVAL, "batch size must be in 1..%d", kMaxBatch);
   if (!grids) return fail(MFR_EINVAL, "grids is NULL");
   b->n = n;
@@ -63,11 +63,11 @@ mfr_status batch_layout(int n, const mfr_grid* grids, int levels, mfr_batch* b, 
     if (grids[k].m[2] == 1 && grids[k].my[2] == 1)
       return fail(MFR_EINVAL, "pair %d: the batched path takes three-dimensional problems only", k);
     size_t per = 0;
-    MFR_TRY(ml_levels(&grids[k], levels, &b->lv[k], &per));
+    MFR_TRY(ml_levels(&grids[k], levels, &b->lv[k], &per, compact));
     size_t cb = 0;
     for (int l = 0; l < levels; ++l) {
       size_t x = 0;
-      MFR_TRY(mfr_workspace_size(&b->lv[k][l].grid, &x));
+      MFR_TRY(ctx_workspace(&b->lv[k][l].grid, compact, &x));
       cb = std::max(cb, x);
     }
     b->ctx_bytes[k] = cb;
@@ -356,6 +356,7 @@ mfr_status mfr_batch_create(int32_t n, const mfr_grid* grids, int32_t levels, vo
   if (!b) return fail(MFR_EINVAL, "host allocation failed");
   size_t need = 0;
   mfr_status s = batch_layout(n, grids, levels, b, &need);
+  if (s == MFR_OK && ws_bytes < need) s = batch_layout(n, grids, levels, b, &need, true);
   if (s == MFR_OK && (!workspace || reinterpret_cast<uintptr_t>(workspace) % 256 != 0))
     s = fail(MFR_EINVAL, "workspace must be non-NULL and 256-byte aligned");
   if (s == MFR_OK && ws_bytes < need)

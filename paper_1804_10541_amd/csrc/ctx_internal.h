@@ -91,8 +91,10 @@ struct Tiling {
   int grid() const { return tiles_x * tiles_y * chunks; }
 };
 
+// compact: chunks of at least 16 planes, so fewer partial blocks, for a workspace
+// that the tiling chosen for speed does not fit.
 Tiling make_tiling(const Geo& g, const std::vector<Conv1>& cx, const std::vector<Conv1>& cy,
-                   const std::vector<Conv1>& cz);
+                   const std::vector<Conv1>& cz, bool compact = false);
 bool valid_shape(const TileShape& s);
 mfr_tile_config current_tile_config();
 void set_tile_config(const mfr_tile_config& c);
@@ -118,7 +120,11 @@ struct Level {
   size_t off_R, off_T, off_u;   // coarse images / displacement (finest: caller buffers)
 };
 
-mfr_status ml_levels(const mfr_grid* finest, int levels, std::vector<Level>* out, size_t* total);
+mfr_status ml_levels(const mfr_grid* finest, int levels, std::vector<Level>* out, size_t* total, bool compact = false);
+
+// Workspace bytes of a context: of the tiling chosen for speed, or (compact) the
+// least that a context accepts.
+mfr_status ctx_workspace(const mfr_grid* grid, bool compact, size_t* bytes);
 
 }  // namespace mfr
 

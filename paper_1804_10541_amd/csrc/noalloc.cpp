@@ -49,7 +49,7 @@ extern "C" {
 mfr_status mfr_hess_vec_noalloc(const mfr_grid* grid, void* hip_stream, const float* R, const float* T,
                                 const float* u, const float* p, float* q) {
   size_t need = 0;
-  MFR_TRY(mfr_workspace_size(grid, &need));
+  MFR_TRY(ctx_workspace(grid, true, &need));
   if (need > kScratchBytes)
     return fail(MFR_ENOMEM,
                 "the problem needs %zu bytes of workspace; mfr_hess_vec_noalloc has %zu (use mfr_create with a "
