@@ -205,6 +205,14 @@ static Range1 groups_touching(const Range1& cols, int T, int tiles) {
   return Range1{lo, std::min(tiles - 1, (cols.hi + 1) / T)};
 }
 
+// Partial slots of the groups touching each node: the first one and their number
+// (they are consecutive modulo sm).
+static std::vector<Range1> slot_ranges(const std::vector<Range1>& groups, int sm) {
+  std::vector<Range1> r(groups.size());
+  for (size_t i = 0; i < groups.size(); ++i) r[i] = Range1{groups[i].lo % sm, groups[i].hi - groups[i].lo + 1};
+  return r;
+}
+
 // The most groups (columns of width T with a one-column ring) overlapping one node's
 // support, and the most chunks of `len` planes holding one node plane.
 static int most_groups(const std::vector<Conv1>& c, int n, int T, int tiles) {
@@ -380,6 +388,16 @@ bool valid_shape(const TileShape& s) {
 
 // ---- workspace layout ---------------------------------------------------------
 
+// Sets of kNodeBlock nodes that a group of a node pass takes, and its groups.
+static int node_sets_per_group(size_t nbar) {
+  const size_t sets = (nbar + kNodeBlock - 1) / kNodeBlock;
+  return (int)((sets + kNodeGroups - 1) / kNodeGroups);
+}
+static int node_groups(size_t nbar) {
+  const size_t sets = (nbar + kNodeBlock - 1) / kNodeBlock, per = node_sets_per_group(nbar);
+  return (int)((sets + per - 1) / per);
+}
+
 Layout make_layout(const Geo& g, const Tiling& t) {
   Layout L;
   size_t o = 0;
@@ -401,9 +419,6 @@ Layout make_layout(const Geo& g, const Tiling& t) {
   L.ntx = take(sizeof(Range1) * g.n[0]);
   L.nty = take(sizeof(Range1) * (plane ? 1 : g.n[1]));
   L.ntz = take(sizeof(Range1) * (plane ? g.n[1] : g.n[2]));
-  L.orgx = take(sizeof(int) * t.tiles_x);
-  L.orgy = take(sizeof(int) * t.tiles_y);
-  L.orgz = take(sizeof(int) * t.chunks);
   L.rx = take(sizeof(Range1) * g.n[0]);
   L.ry = take(sizeof(Range1) * g.n[1]);
   L.rz = take(sizeof(Range1) * g.n[2]);
@@ -420,12 +435,11 @@ Layout make_layout(const Geo& g, const Tiling& t) {
   L.dorgz = take(dg.on ? sizeof(int) * dg.chunks : 0);
   L.dpart = take(dg.on ? sizeof(float) * (size_t)dg.grid() * 3 * dg.nzt * dg.nyt * dg.nxt : 0);
   L.red_tile = take(sizeof(double) * (size_t)t.grid());
-  const size_t node_blocks = (g.nbar + kNodeBlock - 1) / kNodeBlock;
-  L.n_red_node = std::max<size_t>(3 * node_blocks, 2 * 1024);   // node-pass partials (one per block) and others
-  L.red_node = take(sizeof(double) * L.n_red_node);
+  // node-pass partials (one per group) and those of the other vector kernels
+  L.red_node = take(sizeof(double) * std::max(node_groups(g.nbar), 2 * 1024));
+  L.red_vec = take(sizeof(double) * 2 * 1024);       // partials of the CG vector kernels (two per group)
   L.sc = take(sizeof(double) * SC_COUNT);
   L.vec = take(sizeof(float) * nc * g.nbar * 8);   // PCG r z p q diag; GN rhs, trial, direction
-  L.lap = take(sizeof(float) * nc * g.nbar);       // curvature Laplacian (node pass, first half)
   L.div = take(sizeof(float) * g.nbar);           // elastic: divergence per cell of the nodal grid
   L.ctrl = take(sizeof(int) * (2 + ST_COUNT));    // device-steered CG: active flag, state; line-search flag
   L.total = o;
@@ -438,6 +452,11 @@ Layout make_layout(const Geo& g, const Tiling& t) {
 namespace mfr {
 
 
+
+static void set_node_groups(mfr_ctx* c) {
+  c->np.per = node_sets_per_group(c->geo.nbar);
+  c->np_groups = node_groups(c->geo.nbar);
+}
 
 // Context of a two-dimensional problem: tables, the tile kernel's parameters
 // (TileParams with mz = nz = 1), the node pass's view of the n[0] x n[1] node
@@ -472,9 +491,9 @@ static mfr_status ctx_init_plane(mfr_ctx* c, void* stream, void* ws, size_t ws_b
     ntz[i] = Range1{coly[i].lo / t.chunk_len, coly[i].hi / t.chunk_len};
     ry[i] = Range1{std::max(coly[i].lo - 1, 0), std::min(coly[i].hi + 1, g.m[1] - 1)};
   }
-  std::vector<int> orgx(t.tiles_x), orgy(1, 0), orgz(t.chunks);
+  std::vector<int> orgx(t.tiles_x);
   for (int i = 0; i < t.tiles_x; ++i) orgx[i] = cx[std::max(i * TX - 1, 0)].n0;
-  for (int i = 0; i < t.chunks; ++i) orgz[i] = cy[i * t.chunk_len].n0;
+  const auto slx = slot_ranges(ntx, t.smx), sly = slot_ranges(nty, t.smy), slz = slot_ranges(ntz, t.smz);
   const Layout& L = c->lay;
   auto up = [&](size_t off, const void* src, size_t bytes) -> hipError_t {
     return hipMemcpyAsync(c->ws + off, src, bytes, hipMemcpyHostToDevice, c->stream);
@@ -483,12 +502,9 @@ static mfr_status ctx_init_plane(mfr_ctx* c, void* stream, void* ws, size_t ws_b
   HIP_TRY(up(L.cy, cy.data(), sizeof(Conv1) * cy.size()));
   HIP_TRY(up(L.sx, sx.data(), sizeof(Samp1) * sx.size()));
   HIP_TRY(up(L.sy, sy.data(), sizeof(Samp1) * sy.size()));
-  HIP_TRY(up(L.ntx, ntx.data(), sizeof(Range1) * ntx.size()));
-  HIP_TRY(up(L.nty, nty.data(), sizeof(Range1) * nty.size()));
-  HIP_TRY(up(L.ntz, ntz.data(), sizeof(Range1) * ntz.size()));
-  HIP_TRY(up(L.orgx, orgx.data(), sizeof(int) * orgx.size()));
-  HIP_TRY(up(L.orgy, orgy.data(), sizeof(int) * orgy.size()));
-  HIP_TRY(up(L.orgz, orgz.data(), sizeof(int) * orgz.size()));
+  HIP_TRY(up(L.ntx, slx.data(), sizeof(Range1) * slx.size()));
+  HIP_TRY(up(L.nty, sly.data(), sizeof(Range1) * sly.size()));
+  HIP_TRY(up(L.ntz, slz.data(), sizeof(Range1) * slz.size()));
   HIP_TRY(up(L.rx, rx.data(), sizeof(Range1) * rx.size()));
   HIP_TRY(up(L.ry, ry.data(), sizeof(Range1) * ry.size()));
   // tiled diagonal: x tiles as for the tile kernel, row chunks whose blocks hold
@@ -594,11 +610,7 @@ static mfr_status ctx_init_plane(mfr_ctx* c, void* stream, void* ws, size_t ws_b
   q.ntx = at<Range1>(c->ws, L.ntx);
   q.nty = at<Range1>(c->ws, L.nty);
   q.ntz = at<Range1>(c->ws, L.ntz);
-  q.orgx = at<int>(c->ws, L.orgx);
-  q.orgy = at<int>(c->ws, L.orgy);
-  q.orgz = at<int>(c->ws, L.orgz);
   q.red = at<double>(c->ws, L.red_node);
-  q.lap = at<float>(c->ws, L.lap);
   q.live = nullptr;
   c->ctrl = at<int>(c->ws, L.ctrl);
 
@@ -645,6 +657,8 @@ static mfr_status ctx_init_plane(mfr_ctx* c, void* stream, void* ws, size_t ws_b
   c->sc = at<double>(c->ws, L.sc);
   c->red_tile = p.red;
   c->red_node = q.red;
+  c->red_vec = at<double>(c->ws, L.red_vec);
+  set_node_groups(c);
   for (int k = 0; k < 8; ++k) c->vec[k] = at<float>(c->ws, L.vec) + (size_t)k * 2 * g.nbar;
   c->vec_blocks = (int)std::min<size_t>((2 * g.nbar + kVecBlock - 1) / kVecBlock, 1024);
   return MFR_OK;
@@ -700,10 +714,7 @@ mfr_status ctx_init(mfr_ctx* c, const mfr_grid* grid, void* stream, void* ws, si
     const int nbz = std::max(1, std::min(g.n[2], (2048 + nxy - 1) / nxy));
     jbz = node_blocks_z(rz, (g.n[2] + nbz - 1) / nbz);
   }
-  std::vector<int> orgx(t.tiles_x), orgy(t.tiles_y), orgz(t.chunks);
-  for (int i = 0; i < t.tiles_x; ++i) orgx[i] = cx[std::max(i * TX - 1, 0)].n0;
-  for (int i = 0; i < t.tiles_y; ++i) orgy[i] = cy[std::max(i * TY - 1, 0)].n0;
-  for (int i = 0; i < t.chunks; ++i) orgz[i] = cz[i * t.chunk_len].n0;
+  const auto slx = slot_ranges(ntx, t.smx), sly = slot_ranges(nty, t.smy), slz = slot_ranges(ntz, t.smz);
 
   const Layout& L = c->lay;
   auto up = [&](size_t off, const void* src, size_t bytes) -> hipError_t {
@@ -715,12 +726,9 @@ mfr_status ctx_init(mfr_ctx* c, const mfr_grid* grid, void* stream, void* ws, si
   HIP_TRY(up(L.sx, sx.data(), sizeof(Samp1) * sx.size()));
   HIP_TRY(up(L.sy, sy.data(), sizeof(Samp1) * sy.size()));
   HIP_TRY(up(L.sz, sz.data(), sizeof(Samp1) * sz.size()));
-  HIP_TRY(up(L.ntx, ntx.data(), sizeof(Range1) * ntx.size()));
-  HIP_TRY(up(L.nty, nty.data(), sizeof(Range1) * nty.size()));
-  HIP_TRY(up(L.ntz, ntz.data(), sizeof(Range1) * ntz.size()));
-  HIP_TRY(up(L.orgx, orgx.data(), sizeof(int) * orgx.size()));
-  HIP_TRY(up(L.orgy, orgy.data(), sizeof(int) * orgy.size()));
-  HIP_TRY(up(L.orgz, orgz.data(), sizeof(int) * orgz.size()));
+  HIP_TRY(up(L.ntx, slx.data(), sizeof(Range1) * slx.size()));
+  HIP_TRY(up(L.nty, sly.data(), sizeof(Range1) * sly.size()));
+  HIP_TRY(up(L.ntz, slz.data(), sizeof(Range1) * slz.size()));
   HIP_TRY(up(L.rx, rx.data(), sizeof(Range1) * rx.size()));
   HIP_TRY(up(L.ry, ry.data(), sizeof(Range1) * ry.size()));
   HIP_TRY(up(L.rz, rz.data(), sizeof(Range1) * rz.size()));
@@ -853,11 +861,7 @@ mfr_status ctx_init(mfr_ctx* c, const mfr_grid* grid, void* stream, void* ws, si
   q.ntx = at<Range1>(c->ws, L.ntx);
   q.nty = at<Range1>(c->ws, L.nty);
   q.ntz = at<Range1>(c->ws, L.ntz);
-  q.orgx = at<int>(c->ws, L.orgx);
-  q.orgy = at<int>(c->ws, L.orgy);
-  q.orgz = at<int>(c->ws, L.orgz);
   q.red = at<double>(c->ws, L.red_node);
-  q.lap = at<float>(c->ws, L.lap);
   q.live = nullptr;
   c->ctrl = at<int>(c->ws, L.ctrl);
 
@@ -917,6 +921,8 @@ mfr_status ctx_init(mfr_ctx* c, const mfr_grid* grid, void* stream, void* ws, si
   c->sc = at<double>(c->ws, L.sc);
   c->red_tile = p.red;
   c->red_node = q.red;
+  c->red_vec = at<double>(c->ws, L.red_vec);
+  set_node_groups(c);
   for (int k = 0; k < 8; ++k) c->vec[k] = at<float>(c->ws, L.vec) + (size_t)k * 3 * g.nbar;
   c->vec_blocks = (int)std::min<size_t>((3 * g.nbar + kVecBlock - 1) / kVecBlock, 1024);
   return MFR_OK;
@@ -974,7 +980,7 @@ hipError_t enqueue_pcg_diag(mfr_ctx* c, const float* u, float* diag) {
   return launch_safe_diag((int)(c->geo.nc() * c->geo.nbar), diag, c->stream);
 }
 
-int node_blocks(const mfr_ctx* c) { return (int)((c->geo.nbar + kNodeBlock - 1) / kNodeBlock); }
+int node_blocks(const mfr_ctx* c) { return c->np_groups; }
 int node_parts(const mfr_ctx* c) { return node_blocks(c); }   // one partial per block (all components)
 
 mfr_status check_ptr(const void* p, const char* name) {

@@ -100,10 +100,9 @@ mfr_tile_config current_tile_config();
 void set_tile_config(const mfr_tile_config& c);
 
 struct Layout {
-  size_t Tp, cx, cy, cz, sx, sy, sz, ntx, nty, ntz, orgx, orgy, orgz, rx, ry, rz;
-  size_t part, red_tile, red_node, sc, vec, jbx, jby, jbz, lap, ctrl, div;
+  size_t Tp, cx, cy, cz, sx, sy, sz, ntx, nty, ntz, rx, ry, rz;
+  size_t part, red_tile, red_node, red_vec, sc, vec, jbx, jby, jbz, ctrl, div;
   size_t dntx, dnty, dntz, dorgx, dorgy, dorgz, dpart;   // voxel-tiled diagonal
-  size_t n_red_node;
   size_t total;
 };
 
@@ -146,6 +145,8 @@ struct mfr_ctx {
   double* sc;
   double* red_tile;
   double* red_node;
+  double* red_vec;
+  int np_groups;                 // work-groups of a node pass
   float* vec[8];
   int vec_blocks;
   int* ctrl;                     // device-steered CG: [0] active flag, [1..] PcgState
@@ -211,8 +212,8 @@ hipError_t timed(mfr_ctx* c, int slot, F&& launch) {
 
 hipError_t enqueue_diag(mfr_ctx* c, const float* u, float* diag);
 hipError_t enqueue_pcg_diag(mfr_ctx* c, const float* u, float* diag);   // zero entries -> 1
-int node_blocks(const mfr_ctx* c);   // work-groups (per component) of a node pass
-int node_parts(const mfr_ctx* c);    // float64 partials of a gradient / Hv node pass (3 per group)
+int node_blocks(const mfr_ctx* c);   // work-groups of a node pass
+int node_parts(const mfr_ctx* c);    // float64 partials of a gradient / Hv node pass (one per group)
 mfr_status check_ptr(const void* p, const char* name);
 mfr_status enqueue_objective(mfr_ctx* c, const float* u);
 mfr_status read_objective(mfr_ctx* c, double* J, double* D, double* S);

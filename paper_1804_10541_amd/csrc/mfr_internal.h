@@ -11,6 +11,9 @@ namespace mfr {
 
 constexpr int kVecBlock = 256;
 constexpr int kNodeBlock = 256;
+// Most work-groups of a node pass (each leaves one partial, and a CG kernel sums
+// them in every one of its groups); larger grids give a group several node sets.
+constexpr int kNodeGroups = 16384;
 // Longest z chunk of the voxel-tile kernel: a group keeps the per-plane tables of
 // its chunk (plus two planes either side) in LDS.
 constexpr int kMaxChunk = 252;
@@ -25,6 +28,13 @@ __device__ __forceinline__ double ld_coherent(const double* p) {
 }
 __device__ __forceinline__ int ld_coherent(const int* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// XCD-aware order of G work-groups: the hardware dispatches group b to XCD b % 8,
+// so each XCD gets a contiguous range of ids (neighbours share its L2).
+__device__ __forceinline__ int xcd_remap(int b, int G) {
+  const int xcd = b & 7, per = G >> 3, rem = G & 7;
+  return xcd * per + min(xcd, rem) + (b >> 3);
 }
 
 // Grid conversion along one axis (Sec. 4.3, eq. grid_conversion): voxel index
@@ -106,18 +116,15 @@ struct NodeParams {
   int reg;                    // 0 curvature (L L f), 1 diffusive (-L f), 2 elastic (-L f + kappa B^T B f)
   float kappa;                // elastic: (lambda + mu) / mu
   float* div;                 // elastic: divergence per cell ((nx-1)(ny-1)(nz-1) floats), first pass
+  int per;                    // sets of kNodeBlock nodes per work-group
   int tiles_x, tiles_y;
   int nxt, nyt, nzt;
   int smx, smy, smz;          // partial slots per axis (see TileParams)
   const float* part;
-  const Range1* ntx;          // per node index: range of x tiles / y tiles / z chunks
-  const Range1* nty;
+  const Range1* ntx;          // per node index: first slot (lo) and number (hi) of the x tiles /
+  const Range1* nty;          // y tiles / z chunks overlapping it
   const Range1* ntz;
-  const int* orgx;            // per tile: first node index of its partial block
-  const int* orgy;
-  const int* orgz;
   double* red;
-  float* lap;                 // 3 nbar scratch: the curvature Laplacian of the input (first pass)
   const int* live;            // single-problem launches: skip all work while *live == 0 (nullable)
 };
 

@@ -83,155 +83,221 @@ __device__ __forceinline__ float cell_div(const float* __restrict__ f, int nbar,
   return fmaf(sx, ih4x, fmaf(sy, ih4y, sz * ih4z));
 }
 
+// The same for the cell with linear index n, 0 past the last cell.
+__device__ __forceinline__ float elastic_div(const NodeParams& Q, const float* __restrict__ f, int n) {
+  const int cx = Q.nx - 1, cy = Q.ny - 1, cz = Q.nz - 1;
+  if (n >= cx * cy * cz) return 0.0f;
+  const int a = n % cx, b = (n / cx) % cy, c = n / (cx * cy);
+  return cell_div(f, Q.nbar, a, b, c, Q.nx, Q.ny, 0.25f * sqrtf(Q.ihy2x), 0.25f * sqrtf(Q.ihy2y), 0.25f * sqrtf(Q.ihy2z));
+}
+
 }  // namespace
 
-// The curvature part runs in two passes over the nodes: the first stores the
-// 7-point Laplacian L f_d of every node (eq. laplace_discretized) in Q.lap and,
-// for the regulariser value, sums (L f_d)^2; the second reads the Laplacians of
-// the node and its six neighbours (clamped, so a missing neighbour contributes
-// its own value) for L L f_d and adds the gathered tile partials.  Each
-// Laplacian is evaluated once instead of seven times; the floats are the same
-// as evaluating them in place.
-template <int MODE>
-__device__ __forceinline__ void lap_body(const NodeParams& Q, const float* __restrict__ f, const int blk,
-                                         double* sred) {
-  const int n = blk * kNodeBlock + threadIdx.x;
+// A work-group takes `per` consecutive sets of kNodeBlock nodes (1 up to 4 M nodes,
+// so that at most kNodeGroups partials are left whatever the grid), and neighbouring
+// groups run on one XCD: the stencil's rows and planes are read through its L2.
+__device__ __forceinline__ int node_sets(const NodeParams& Q) { return (Q.nbar + kNodeBlock - 1) / kNodeBlock; }
+
+struct NodeIdx {
+  int n, i, j, k;
+};
+__device__ __forceinline__ NodeIdx node_index(const NodeParams& Q, int n) {
+  const int r = n / Q.nx, i = n - r * Q.nx, k = r / Q.ny;
+  return NodeIdx{n, i, r - k * Q.ny, k};
+}
+
+// Regulariser value only: curvature sum (L f)^2 (eq. laplace_discretized);
+// diffusive and elastic the squared edge differences, elastic also kappa times
+// the squared divergence of the cell with the node's linear index.
+__device__ __forceinline__ void reg_value_body(const NodeParams& Q, const float* __restrict__ f, const int vb,
+                                               double* sred) {
   double local = 0.0;
-  if (n < Q.nbar) {
-    const int i = n % Q.nx;
-    const int j = (n / Q.nx) % Q.ny;
-    const int k = n / (Q.nx * Q.ny);
+  const int last = min((vb + 1) * Q.per, node_sets(Q));
+  for (int set = vb * Q.per; set < last; ++set) {
+    const NodeIdx x = node_index(Q, set * kNodeBlock + threadIdx.x);
+    if (x.n >= Q.nbar) break;
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
       if (d >= Q.nc) break;
-      const float L0 = lap7(f + (size_t)d * Q.nbar, i, j, k, Q.nx, Q.ny, Q.nz, Q.ihy2x, Q.ihy2y, Q.ihy2z);
-      Q.lap[(size_t)d * Q.nbar + n] = L0;
-      // curvature: sum (L f)^2; diffusive and elastic: the squared edge differences
-      if (MODE == NP_S)
-        local += Q.reg ? (double)fwd_sq(f + (size_t)d * Q.nbar, i, j, k, Q.nx, Q.ny, Q.nz, Q.ihy2x, Q.ihy2y, Q.ihy2z)
-                       : (double)L0 * (double)L0;
+      const float* fd = f + (size_t)d * Q.nbar;
+      if (Q.reg) {
+        local += (double)fwd_sq(fd, x.i, x.j, x.k, Q.nx, Q.ny, Q.nz, Q.ihy2x, Q.ihy2y, Q.ihy2z);
+      } else {
+        const float L0 = lap7(fd, x.i, x.j, x.k, Q.nx, Q.ny, Q.nz, Q.ihy2x, Q.ihy2y, Q.ihy2z);
+        local += (double)L0 * (double)L0;
+      }
+    }
+    if (Q.reg == 2) {
+      const float dv = elastic_div(Q, f, x.n);
+      local += (double)Q.kappa * (double)dv * (double)dv;
     }
   }
-  if (Q.reg == 2) {   // elastic: divergence of the cell with linear index n, kept for the second pass
-    const int cx = Q.nx - 1, cy = Q.ny - 1, cz = Q.nz - 1;
-    if (n < cx * cy * cz) {
-      const int a = n % cx, b = (n / cx) % cy, c = n / (cx * cy);
-      const float dv = cell_div(f, Q.nbar, a, b, c, Q.nx, Q.ny, 0.25f * sqrtf(Q.ihy2x), 0.25f * sqrtf(Q.ihy2y),
-                                0.25f * sqrtf(Q.ihy2z));
-      Q.div[n] = dv;
-      if (MODE == NP_S) local += (double)Q.kappa * (double)dv * (double)dv;
-    }
+  const double s = block_sum<kNodeBlock>(local, sred);
+  if (threadIdx.x == 0) Q.red[vb] = s;
+}
+
+// Elastic: the divergence of the cell with linear index n, kept for the node pass.
+__device__ __forceinline__ void div_body(const NodeParams& Q, const float* __restrict__ f, const int vb) {
+  const int last = min((vb + 1) * Q.per, node_sets(Q));
+  for (int set = vb * Q.per; set < last; ++set) {
+    const int n = set * kNodeBlock + threadIdx.x;
+    if (n < (Q.nx - 1) * (Q.ny - 1) * (Q.nz - 1)) Q.div[n] = elastic_div(Q, f, n);
   }
-  if (MODE == NP_S) {
-    const double s = block_sum<kNodeBlock>(local, sred);
-    if (threadIdx.x == 0) Q.red[blk] = s;
+}
+
+// L f and L L f of one component at a node (curvature), from the 25 points of the
+// twice applied 7-point Laplacian with clamped neighbours; the floats are those of
+// applying it twice (a missing neighbour of the second one contributes the node's
+// own Laplacian).  Bound by latency on small grids and by the caches' request rate
+// on large ones.  Reading the 25 points through the caches replaced a pass that
+// stored L f of every node and a second one that read seven of them: one launch less
+// and 24 bytes less per node and component.  Both passes together, before and now (a
+// Hessian product, event times): 65x65x49 nodes 19.6 -> 11.5 us, 129x129x225 134 ->
+// 104 us, 2049x2049 76 -> 46 us.  One instance per regulariser: with all of them in
+// one kernel it took 97 registers and 200 us at 129x129x225.
+template <bool PLANE>
+__device__ __forceinline__ float lap_lap(const float* __restrict__ f, const NodeParams& Q, const NodeIdx& x, float& L0) {
+  const int nxy = Q.nx * Q.ny;
+  const int xm = -(x.i > 0), xp = x.i < Q.nx - 1, xm2 = x.i > 1 ? -2 : xm, xp2 = x.i < Q.nx - 2 ? 2 : xp;
+  const int zm = x.k > 0 ? -nxy : 0, zp = x.k < Q.nz - 1 ? nxy : 0;
+  const int zm2 = x.k > 1 ? -2 * nxy : zm, zp2 = x.k < Q.nz - 2 ? 2 * nxy : zp;
+  const float* c = f + x.n;
+  const float f0 = c[0];
+  const float fxm = c[xm], fxp = c[xp], fzm = c[zm], fzp = c[zp];
+  const float fxm2 = c[xm2], fxp2 = c[xp2], fzm2 = c[zm2], fzp2 = c[zp2];
+  const float mm = c[xm + zm], mp = c[xm + zp], pm = c[xp + zm], pp = c[xp + zp];
+  // neighbours along y of a point and the point itself: (a + b) - 2 v, 0 with one node along y
+  float y0 = 0.f, yxm = 0.f, yxp = 0.f, yzm = 0.f, yzp = 0.f, Lym = 0.f, Lyp = 0.f;
+  const float m0 = -2.0f * f0, mxm = -2.0f * fxm, mxp = -2.0f * fxp, mzm = -2.0f * fzm, mzp = -2.0f * fzp;
+  if constexpr (!PLANE) {
+    const int ym = x.j > 0 ? -Q.nx : 0, yp = x.j < Q.ny - 1 ? Q.nx : 0;
+    const int ym2 = x.j > 1 ? -2 * Q.nx : ym, yp2 = x.j < Q.ny - 2 ? 2 * Q.nx : yp;
+    const float fym = c[ym], fyp = c[yp], fym2 = c[ym2], fyp2 = c[yp2];
+    const float xmym = c[xm + ym], xmyp = c[xm + yp], xpym = c[xp + ym], xpyp = c[xp + yp];
+    const float ymzm = c[ym + zm], ymzp = c[ym + zp], ypzm = c[yp + zm], ypzp = c[yp + zp];
+    y0 = fym + fyp + m0;
+    yxm = xmym + xmyp + mxm;
+    yxp = xpym + xpyp + mxp;
+    yzm = ymzm + ypzm + mzm;
+    yzp = ymzp + ypzp + mzp;
+    const float mym = -2.0f * fym, myp = -2.0f * fyp;
+    Lym = fmaf(xmym + xpym + mym, Q.ihy2x, fmaf(fym2 + f0 + mym, Q.ihy2y, (ymzm + ymzp + mym) * Q.ihy2z));
+    Lyp = fmaf(xmyp + xpyp + myp, Q.ihy2x, fmaf(f0 + fyp2 + myp, Q.ihy2y, (ypzm + ypzp + myp) * Q.ihy2z));
   }
+  L0 = fmaf(fxm + fxp + m0, Q.ihy2x, fmaf(y0, Q.ihy2y, (fzm + fzp + m0) * Q.ihy2z));
+  const float Lxm = xm ? fmaf(fxm2 + f0 + mxm, Q.ihy2x, fmaf(yxm, Q.ihy2y, (mm + mp + mxm) * Q.ihy2z)) : L0;
+  const float Lxp = xp ? fmaf(f0 + fxp2 + mxp, Q.ihy2x, fmaf(yxp, Q.ihy2y, (pm + pp + mxp) * Q.ihy2z)) : L0;
+  const float Lzm = zm ? fmaf(mm + pm + mzm, Q.ihy2x, fmaf(yzm, Q.ihy2y, (fzm2 + f0 + mzm) * Q.ihy2z)) : L0;
+  const float Lzp = zp ? fmaf(mp + pp + mzp, Q.ihy2x, fmaf(yzp, Q.ihy2y, (f0 + fzp2 + mzp) * Q.ihy2z)) : L0;
+  if (x.j == 0) Lym = L0;
+  if (x.j == Q.ny - 1) Lyp = L0;
+  const float m2 = -2.0f * L0;
+  return fmaf(Lxm + Lxp + m2, Q.ihy2x, fmaf(Lym + Lyp + m2, Q.ihy2y, (Lzm + Lzp + m2) * Q.ihy2z));
 }
 
 // One thread per node, all its components d: q_d = s_ngf * (sum of the tile
 // partials of component d) + s_curv * (L L f_d).  The node's indices and the
 // walk over the tile slots that overlap it are formed once for all components.
-// Partials: red[blk] (the components summed in order within the thread).
-template <int MODE>
+// Partials: red[vb] (the components summed in order within the thread).
+// REG: the regulariser; PLANE: a two-dimensional problem (two components, one node
+// along y in this view; curvature only).
+template <int MODE, int REG, bool PLANE>
 __device__ __forceinline__ void node_pass_body(const NodeParams& Q, const float* __restrict__ f,
-                                               float* __restrict__ out, const int blk, double* sred) {
-  const int n = blk * kNodeBlock + threadIdx.x;
+                                               float* __restrict__ out, const int vb, double* sred) {
+  constexpr int NC = PLANE ? 2 : 3;
   double local = 0.0;
-  if (n < Q.nbar) {
-    const int i = n % Q.nx;
-    const int j = (n / Q.nx) % Q.ny;
-    const int k = n / (Q.nx * Q.ny);
-    const int nxy = Q.nx * Q.ny;
-    const size_t nb3 = (size_t)Q.nbar;
-    // gather of the transposed conversion: every tile slot overlapping node n
-    // (the groups overlapping a node have distinct slots: at most smx of them
-    // along x, and so on)
+  const size_t nb3 = (size_t)Q.nbar;
+  const int last = min((vb + 1) * Q.per, node_sets(Q));
+  for (int set = vb * Q.per; set < last; ++set) {
+    const NodeIdx x = node_index(Q, set * kNodeBlock + threadIdx.x);
+    const int n = x.n, i = x.i, j = x.j, k = x.k;
+    if (n >= Q.nbar) break;
+    // gather of the transposed conversion: every tile slot overlapping node n (the
+    // groups overlapping a node have consecutive slots, modulo smx along x and so on;
+    // the tables hold the first slot and the number of them)
     const Range1 rx = Q.ntx[i], ry = Q.nty[j], rz = Q.ntz[k];
-    // slot indices c % sm advance with c (one remainder per axis)
     float sg[3] = {0.0f, 0.0f, 0.0f};
-    const int sx0 = rx.lo % Q.smx, sy0 = ry.lo % Q.smy;
-    for (int cz = rz.lo, sz = rz.lo % Q.smz; cz <= rz.hi; ++cz, sz = sz + 1 == Q.smz ? 0 : sz + 1) {
-      for (int cy = ry.lo, sy = sy0; cy <= ry.hi; ++cy, sy = sy + 1 == Q.smy ? 0 : sy + 1) {
+    for (int cz = 0, sz = rz.lo; cz < rz.hi; ++cz, sz = sz + 1 == Q.smz ? 0 : sz + 1) {
+      for (int cy = 0, sy = ry.lo; cy < ry.hi; ++cy, sy = sy + 1 == Q.smy ? 0 : sy + 1) {
         const size_t pzy = (size_t)sz * Q.smy + sy;
-        for (int cx = rx.lo, sx = sx0; cx <= rx.hi; ++cx, sx = sx + 1 == Q.smx ? 0 : sx + 1) {
+        for (int cx = 0, sx = rx.lo; cx < rx.hi; ++cx, sx = sx + 1 == Q.smx ? 0 : sx + 1) {
           const float* pp = Q.part + (pzy * Q.smx + sx) * 3 * nb3 + n;
 #pragma unroll
           for (int d = 0; d < 3; ++d)
-            if (d < Q.nc) sg[d] += pp[d * nb3];
+            if (d < NC) sg[d] += pp[d * nb3];
         }
       }
     }
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
-      if (d >= Q.nc) break;
+      if (d >= NC) break;
       const float* fd = f + (size_t)d * nb3;
-      const float* Ld = Q.lap + (size_t)d * nb3;
-      const float L0 = Ld[n];
-      const float Lxm = i > 0 ? Ld[n - 1] : L0;
-      const float Lxp = i < Q.nx - 1 ? Ld[n + 1] : L0;
-      const float Lym = j > 0 ? Ld[n - Q.nx] : L0;
-      const float Lyp = j < Q.ny - 1 ? Ld[n + Q.nx] : L0;
-      const float Lzm = k > 0 ? Ld[n - nxy] : L0;
-      const float Lzp = k < Q.nz - 1 ? Ld[n + nxy] : L0;
-      const float m2 = -2.0f * L0;
-      // curvature: L L f; diffusive: -L f (its Hessian is -hbar^y L); elastic: -L f + kappa (B^T B f)_d
-      float LL = Q.reg ? -L0 : fmaf(Lxm + Lxp + m2, Q.ihy2x, fmaf(Lym + Lyp + m2, Q.ihy2y, (Lzm + Lzp + m2) * Q.ihy2z));
-      if (Q.reg == 2) {
-        const int cx = Q.nx - 1, cy = Q.ny - 1;
-        const int nd = d == 0 ? i : d == 1 ? j : k;
-        const float ih4 = 0.25f * sqrtf(d == 0 ? Q.ihy2x : d == 1 ? Q.ihy2y : Q.ihy2z);
-        float bt = 0.f;
-        for (int c = max(k - 1, 0); c <= min(k, Q.nz - 2); ++c)
-          for (int b = max(j - 1, 0); b <= min(j, Q.ny - 2); ++b)
-            for (int a = max(i - 1, 0); a <= min(i, Q.nx - 2); ++a) {
-              const int cd = d == 0 ? a : d == 1 ? b : c;
-              const float dv = Q.div[a + cx * (b + cy * c)];
-              bt += cd == nd - 1 ? dv : -dv;   // the node is the upper (+) or lower (-) corner along d
-            }
-        LL = fmaf(Q.kappa * ih4, bt, LL);
+      float LL, L0 = 0.f;
+      if constexpr (REG == 0) {
+        LL = lap_lap<PLANE>(fd, Q, x, L0);
+      } else {
+        // diffusive: -L f (its Hessian is -hbar^y L); elastic: -L f + kappa (B^T B f)_d
+        LL = -lap7(fd, i, j, k, Q.nx, Q.ny, Q.nz, Q.ihy2x, Q.ihy2y, Q.ihy2z);
+        if constexpr (REG == 2) {
+          const int cx = Q.nx - 1, cy = Q.ny - 1;
+          const int nd = d == 0 ? i : d == 1 ? j : k;
+          const float ih4 = 0.25f * sqrtf(d == 0 ? Q.ihy2x : d == 1 ? Q.ihy2y : Q.ihy2z);
+          float bt = 0.f;
+          for (int c = max(k - 1, 0); c <= min(k, Q.nz - 2); ++c)
+            for (int b = max(j - 1, 0); b <= min(j, Q.ny - 2); ++b)
+              for (int a = max(i - 1, 0); a <= min(i, Q.nx - 2); ++a) {
+                const int cd = d == 0 ? a : d == 1 ? b : c;
+                const float dv = Q.div[a + cx * (b + cy * c)];
+                bt += cd == nd - 1 ? dv : -dv;   // the node is the upper (+) or lower (-) corner along d
+              }
+          LL = fmaf(Q.kappa * ih4, bt, LL);
+        }
       }
       const float q = fmaf(Q.s_ngf, sg[d], Q.s_curv * LL);
       out[(size_t)d * nb3 + n] = q;
       if (MODE == NP_GRAD) {
-        local += Q.reg ? (double)fwd_sq(fd, i, j, k, Q.nx, Q.ny, Q.nz, Q.ihy2x, Q.ihy2y, Q.ihy2z)
+        local += REG ? (double)fwd_sq(fd, i, j, k, Q.nx, Q.ny, Q.nz, Q.ihy2x, Q.ihy2y, Q.ihy2z)
                        : (double)L0 * (double)L0;
-        if (Q.reg == 2 && d == 0 && n < (Q.nx - 1) * (Q.ny - 1) * (Q.nz - 1))
+        if (REG == 2 && d == 0 && n < (Q.nx - 1) * (Q.ny - 1) * (Q.nz - 1))
           local += (double)Q.kappa * (double)Q.div[n] * (double)Q.div[n];   // once per cell (component row 0)
       }
       if (MODE == NP_HV) local += (double)fd[n] * (double)q;
     }
   }
   const double s = block_sum<kNodeBlock>(local, sred);
-  if (threadIdx.x == 0) Q.red[blk] = s;
+  if (threadIdx.x == 0) Q.red[vb] = s;
 }
 
-template <int MODE>
-__global__ __launch_bounds__(kNodeBlock) void lap_kernel(const NodeParams Q, const float* __restrict__ f) {
+__global__ __launch_bounds__(kNodeBlock) void reg_value_kernel(const NodeParams Q, const float* __restrict__ f) {
   if (Q.live && !ld_coherent(Q.live)) return;   // a device-steered solve has stopped
   __shared__ double sred[kNodeBlock / 64];
-  lap_body<MODE>(Q, f, blockIdx.x, sred);
+  reg_value_body(Q, f, xcd_remap(blockIdx.x, gridDim.x), sred);
 }
 
-template <int MODE>
-__global__ __launch_bounds__(kNodeBlock) void lap_batch_kernel(const NodeJobs J) {
+__global__ __launch_bounds__(kNodeBlock) void reg_value_batch_kernel(const NodeJobs J) {
   __shared__ double sred[kNodeBlock / 64];
   int pr = 0;
   while (pr + 1 < J.n && J.prefix[pr + 1] <= (int)blockIdx.x) ++pr;
   if (J.active && !ld_coherent(J.active + pr)) return;
   const NodeJob& jb = J.jobs[pr];
-  lap_body<MODE>(jb.q, jb.f, blockIdx.x - J.prefix[pr], sred);
+  reg_value_body(jb.q, jb.f, xcd_remap(blockIdx.x - J.prefix[pr], J.prefix[pr + 1] - J.prefix[pr]), sred);
 }
 
-template <int MODE>
+__global__ __launch_bounds__(kNodeBlock) void div_kernel(const NodeParams Q, const float* __restrict__ f) {
+  if (Q.live && !ld_coherent(Q.live)) return;   // a device-steered solve has stopped
+  div_body(Q, f, xcd_remap(blockIdx.x, gridDim.x));
+}
+
+template <int MODE, int REG, bool PLANE>
 __global__ __launch_bounds__(kNodeBlock) void node_pass_kernel(const NodeParams Q,
                                                                const float* __restrict__ f,
                                                                float* __restrict__ out) {
   if (Q.live && !ld_coherent(Q.live)) return;   // a device-steered solve has stopped
   __shared__ double sred[kNodeBlock / 64];
-  node_pass_body<MODE>(Q, f, out, blockIdx.x, sred);
+  node_pass_body<MODE, REG, PLANE>(Q, f, out, xcd_remap(blockIdx.x, gridDim.x), sred);
 }
 
-// The same per-node arithmetic for a table of problems (batched path).
+// The same per-node arithmetic for a table of problems (batched path; curvature only).
 template <int MODE>
 __global__ __launch_bounds__(kNodeBlock) void node_pass_batch_kernel(const NodeJobs J) {
   __shared__ double sred[kNodeBlock / 64];
@@ -239,40 +305,47 @@ __global__ __launch_bounds__(kNodeBlock) void node_pass_batch_kernel(const NodeJ
   while (pr + 1 < J.n && J.prefix[pr + 1] <= (int)blockIdx.x) ++pr;
   if (J.active && !ld_coherent(J.active + pr)) return;
   const NodeJob& jb = J.jobs[pr];
-  node_pass_body<MODE>(jb.q, jb.f, jb.out, blockIdx.x - J.prefix[pr], sred);
+  node_pass_body<MODE, 0, false>(jb.q, jb.f, jb.out, xcd_remap(blockIdx.x - J.prefix[pr], J.prefix[pr + 1] - J.prefix[pr]), sred);
 }
 
 hipError_t launch_node_pass_batch(int mode, const NodeJobs& j, hipStream_t st) {
   const int blocks = j.prefix[j.n];
-  if (mode == NP_S) {
-    hipLaunchKernelGGL(lap_batch_kernel<NP_S>, dim3(blocks), dim3(kNodeBlock), 0, st, j);
-    return hipGetLastError();
-  }
-  hipLaunchKernelGGL(lap_batch_kernel<NP_HV>, dim3(blocks), dim3(kNodeBlock), 0, st, j);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if (mode == NP_GRAD)
+  if (mode == NP_S)
+    hipLaunchKernelGGL(reg_value_batch_kernel, dim3(blocks), dim3(kNodeBlock), 0, st, j);
+  else if (mode == NP_GRAD)
     hipLaunchKernelGGL(node_pass_batch_kernel<NP_GRAD>, dim3(blocks), dim3(kNodeBlock), 0, st, j);
   else
     hipLaunchKernelGGL(node_pass_batch_kernel<NP_HV>, dim3(blocks), dim3(kNodeBlock), 0, st, j);
   return hipGetLastError();
 }
 
+template <int MODE>
+static hipError_t launch_node_mode(const NodeParams& q, const float* f, float* out, int blocks, hipStream_t st) {
+  const dim3 g(blocks), b(kNodeBlock);
+  if (q.nc == 2)
+    hipLaunchKernelGGL((node_pass_kernel<MODE, 0, true>), g, b, 0, st, q, f, out);
+  else if (q.reg == 0)
+    hipLaunchKernelGGL((node_pass_kernel<MODE, 0, false>), g, b, 0, st, q, f, out);
+  else if (q.reg == 1)
+    hipLaunchKernelGGL((node_pass_kernel<MODE, 1, false>), g, b, 0, st, q, f, out);
+  else
+    hipLaunchKernelGGL((node_pass_kernel<MODE, 2, false>), g, b, 0, st, q, f, out);
+  return hipGetLastError();
+}
 
 hipError_t launch_node_pass(int mode, const NodeParams& q, const float* f, float* out, int blocks,
                             hipStream_t st) {
   if (mode == NP_S) {
-    hipLaunchKernelGGL(lap_kernel<NP_S>, dim3(blocks), dim3(kNodeBlock), 0, st, q, f);
+    hipLaunchKernelGGL(reg_value_kernel, dim3(blocks), dim3(kNodeBlock), 0, st, q, f);
     return hipGetLastError();
   }
-  hipLaunchKernelGGL(lap_kernel<NP_HV>, dim3(blocks), dim3(kNodeBlock), 0, st, q, f);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if (mode == NP_GRAD)
-    hipLaunchKernelGGL(node_pass_kernel<NP_GRAD>, dim3(blocks), dim3(kNodeBlock), 0, st, q, f, out);
-  else
-    hipLaunchKernelGGL(node_pass_kernel<NP_HV>, dim3(blocks), dim3(kNodeBlock), 0, st, q, f, out);
-  return hipGetLastError();
+  if (q.reg == 2) {   // elastic: the cells' divergence first
+    hipLaunchKernelGGL(div_kernel, dim3(blocks), dim3(kNodeBlock), 0, st, q, f);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  if (mode == NP_GRAD) return launch_node_mode<NP_GRAD>(q, f, out, blocks, st);
+  return launch_node_mode<NP_HV>(q, f, out, blocks, st);
 }
 
 // Fixed-order sum of n float64 partials by one work-group.

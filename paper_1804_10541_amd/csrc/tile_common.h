@@ -24,13 +24,7 @@ __device__ __forceinline__ void block_sum_store(double v, double* out, double* s
   }
 }
 
-// XCD-aware block order: hardware dispatches block b to XCD b % 8, so give each
-// XCD a contiguous range of tile ids (neighbouring tiles share its L2).
-__device__ __forceinline__ int xcd_block_id() {
-  const int G = gridDim.x, b = blockIdx.x;
-  const int xcd = b & 7, per = G >> 3, rem = G & 7;
-  return xcd * per + min(xcd, rem) + (b >> 3);
-}
+__device__ __forceinline__ int xcd_block_id() { return xcd_remap(blockIdx.x, gridDim.x); }
 
 struct Tri {
   float v, gx, gy, gz;
