@@ -1080,7 +1080,7 @@ mfr_status pcg_run_steered(mfr_ctx* c, const float* u, const float* b, float* s_
   v.diag = diag;
   v.sc = c->sc;
   v.state = c->ctrl + 1;
-  v.red = c->red_node;
+  v.red = c->red_vec;
   v.red_pq = c->red_node;
   v.n_pq = node_parts(c);
   v.n3 = (int)(c->geo.nc() * c->geo.nbar);
@@ -1100,10 +1100,8 @@ mfr_status pcg_run_steered(mfr_ctx* c, const float* u, const float* b, float* s_
     for (int i = 0; i < o->max_iter; ++i) {
       HIP_TRY(timed(c, 2, [&] { return launch_tiles(c, MODE_HV, tp, u, v.p); }));
       HIP_TRY(timed(c, 4, [&] { return launch_node_pass(NP_HV, np, v.p, v.q, node_blocks(c), c->stream); }));
-      HIP_TRY(launch_pcg_alpha_batch(V, c->stream));
       HIP_TRY(launch_pcg_update_batch(V, c->stream));
-      HIP_TRY(launch_pcg_beta_batch(V, c->stream));
-      HIP_TRY(launch_pcg_direction_batch(V, c->stream));
+      HIP_TRY(launch_pcg_step_batch(V, c->stream));
     }
     HIP_TRY(launch_pcg_info_out(c->ctrl + 1, c->sc, info_dev, c->stream));
     return MFR_OK;
@@ -1113,10 +1111,8 @@ mfr_status pcg_run_steered(mfr_ctx* c, const float* u, const float* b, float* s_
     for (int i = 0; i < k; ++i) {
       HIP_TRY(timed(c, 2, [&] { return launch_tiles(c, MODE_HV, tp, u, v.p); }));
       HIP_TRY(timed(c, 4, [&] { return launch_node_pass(NP_HV, np, v.p, v.q, node_blocks(c), c->stream); }));
-      HIP_TRY(launch_pcg_alpha_batch(V, c->stream));
       HIP_TRY(launch_pcg_update_batch(V, c->stream));
-      HIP_TRY(launch_pcg_beta_batch(V, c->stream));
-      HIP_TRY(launch_pcg_direction_batch(V, c->stream));
+      HIP_TRY(launch_pcg_step_batch(V, c->stream));
     }
     done += k;
     HIP_TRY(hipMemcpyAsync(&active, c->ctrl, sizeof(int), hipMemcpyDeviceToHost, c->stream));
@@ -1166,7 +1162,7 @@ mfr_status pcg_run_flexible(mfr_ctx* c, const float* u, const float* b, float* s
   v.diag = nullptr;   // start: z = r, replaced by the network below
   v.sc = c->sc;
   v.state = state;
-  v.red = c->red_node;
+  v.red = c->red_vec;
   v.red_pq = c->red_node;
   v.n_pq = node_parts(c);
   v.n3 = n3;
@@ -1208,13 +1204,12 @@ mfr_status pcg_run_flexible(mfr_ctx* c, const float* u, const float* b, float* s
       const int it = done + i + 1;
       HIP_TRY(timed(c, 2, [&] { return launch_tiles(c, MODE_HV, tp, u, p); }));
       HIP_TRY(timed(c, 4, [&] { return launch_node_pass(NP_HV, np, p, q, node_blocks(c), c->stream); }));
-      HIP_TRY(launch_pcg_alpha_batch(V, c->stream));
       if (jacobi) {
         HIP_TRY(launch_pcg_update_batch(VJ, c->stream));
-        HIP_TRY(launch_pcg_beta_batch(VJ, c->stream));
-        HIP_TRY(launch_pcg_direction_batch(VJ, c->stream));
+        HIP_TRY(launch_pcg_step_batch(VJ, c->stream));
         continue;
       }
+      HIP_TRY(launch_pcg_alpha_batch(V, c->stream));
       // s += alpha p, r_prev = r, r -= alpha q; |r|, the convergence test, the RMS scales
       HIP_TRY(launch_fpcg_update(n3, diag, p, q, s_out, r, r_prev, c->sc, c->red_node, vb, c->stream, active));
       HIP_TRY(launch_fpcg_scales(c->red_node, vb, n3, c->sc, pc_scalars(c->pc), c->stream, state, active));

@@ -249,7 +249,7 @@ VecJobs vec_jobs(mfr_batch* b, const int* max_iter, double rtol, bool precond) {
     v.diag = precond ? c->vec[4] : nullptr;
     v.sc = b->sc + SC_COUNT * k;
     v.state = b->state + ST_COUNT * k;
-    v.red = c->red_node;
+    v.red = c->red_vec;
     v.red_pq = c->red_node;
     v.n_pq = node_parts(c);
     v.n3 = (int)(3 * c->geo.nbar);
@@ -270,10 +270,8 @@ mfr_status cg_iteration(mfr_batch* b, const VecJobs& V, const float* const* u) {
     q[k] = V.jobs[k].q;
   }
   MFR_TRY(batch_hv(b, u, p, q, b->active));
-  HIP_TRY(launch_pcg_alpha_batch(V, b->st));
   HIP_TRY(launch_pcg_update_batch(V, b->st));
-  HIP_TRY(launch_pcg_beta_batch(V, b->st));
-  HIP_TRY(launch_pcg_direction_batch(V, b->st));
+  HIP_TRY(launch_pcg_step_batch(V, b->st));
   return MFR_OK;
 }
 

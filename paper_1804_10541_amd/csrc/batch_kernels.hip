@@ -181,7 +181,7 @@ hipError_t launch_pcg_init_batch(const VecJobs& j, hipStream_t st) {
   return hipGetLastError();
 }
 
-// alpha = r.z / p.q from the node-pass partials; breakdown ends the problem.
+// alpha = r.z / p.q from the node-pass partials (flexible solve); breakdown ends the problem.
 // One 1024-thread group per problem with two independent running sums per thread
 // (a fixed order, so the result does not depend on timing).
 __global__ __launch_bounds__(1024) void pcg_alpha_batch_kernel(const VecJobs J) {
@@ -216,13 +216,56 @@ hipError_t launch_pcg_alpha_batch(const VecJobs& j, hipStream_t st) {
   return hipGetLastError();
 }
 
+// ---- one CG iteration after the node pass: two launches --------------------------
+// Every group sums the partials of the preceding kernel itself (at most kNodeGroups
+// or 2 x 1024 float64 values, read through L2) in the same fixed order, so all of
+// them hold the same alpha (beta) and the same verdict, and the first group of a
+// problem writes the scalars and the control state.  The kernels with one group per
+// problem that formed alpha and beta took 4.5 us each, plus their launch gaps, for
+// a few hundred additions.  Nothing that a group reads here is written by another
+// group of the same launch, except the active flag, which only ever turns the
+// remaining groups of a solve that has just stopped into no-ops: their vectors are
+// not used any more.
+__device__ __forceinline__ double sum_parts(const double* __restrict__ parts, int n, double* sred, double* stot) {
+  double a = 0.0, b = 0.0;
+  int i = threadIdx.x;
+  for (; i + kVecBlock < n; i += 2 * kVecBlock) {
+    a += parts[i];
+    b += parts[i + kVecBlock];
+  }
+  if (i < n) a += parts[i];
+  const double s = block_sum<kVecBlock>(a + b, sred);
+  if (threadIdx.x == 0) *stot = s;
+  __syncthreads();
+  return *stot;
+}
+
+// alpha = r.z / p.q (a breakdown, p.q <= 0 or not finite, ends the problem without
+// the update); s += alpha p, r -= alpha q, z = M^-1 r; partials of r.r and r.z.
 __global__ __launch_bounds__(kVecBlock) void pcg_update_batch_kernel(const VecJobs J) {
-  __shared__ double sred[kVecBlock / 64];
+  __shared__ double sred[kVecBlock / 64], stot;
   const int pr = find_job(J.prefix, J.n, blockIdx.x);
   const VecJob& v = J.jobs[pr];
   if (!ld_coherent(v.state + ST_ACTIVE)) return;
   const int lb = blockIdx.x - J.prefix[pr], nb = J.prefix[pr + 1] - J.prefix[pr];
-  const float alpha = (float)ld_coherent(v.sc + SC_ALPHA);
+  const double rz_old = ld_coherent(v.sc + SC_RZ);
+  const double pq = sum_parts(v.red_pq, v.n_pq, sred, &stot);
+  const bool ok = pq > 0.0 && isfinite(pq);
+  const double alpha_d = ok ? rz_old / pq : 0.0;
+  if (lb == 0 && threadIdx.x == 0) {
+    double* sc = v.sc;
+    sc[SC_PQ] = pq;
+    sc[SC_ALPHA] = alpha_d;
+    sc[SC_RZOLD] = rz_old;
+    v.state[ST_NEXT] = ld_coherent(v.state + ST_ITERS) + 1;
+    if (!ok) {
+      v.state[ST_FLAG] = 2;
+      v.state[ST_ACTIVE] = 0;
+      J.active_out[pr] = 0;
+    }
+  }
+  if (!ok) return;
+  const float alpha = (float)alpha_d;
   double rr = 0.0, rz = 0.0;
   for (int i = lb * kVecBlock + threadIdx.x; i < v.n3; i += nb * kVecBlock) {
     const float ri = fmaf(-alpha, v.q[i], v.r[i]);
@@ -236,8 +279,8 @@ __global__ __launch_bounds__(kVecBlock) void pcg_update_batch_kernel(const VecJo
   const double a = block_sum<kVecBlock>(rr, sred);
   const double b = block_sum<kVecBlock>(rz, sred);
   if (threadIdx.x == 0) {
-    v.red[2 * lb] = a;
-    v.red[2 * lb + 1] = b;
+    v.red[lb] = a;
+    v.red[nb + lb] = b;
   }
 }
 
@@ -246,48 +289,47 @@ hipError_t launch_pcg_update_batch(const VecJobs& j, hipStream_t st) {
   return hipGetLastError();
 }
 
-// rr, rz_new, beta; convergence and iteration limit end the problem.
-__global__ __launch_bounds__(256) void pcg_beta_batch_kernel(const VecJobs J) {
-  __shared__ double sred[4];
-  const int pr = blockIdx.x;
+// |r|, beta = (r.z)_new / (r.z)_old and the convergence test; p = z + beta p unless
+// the solve has stopped.
+__global__ __launch_bounds__(kVecBlock) void pcg_step_batch_kernel(const VecJobs J) {
+  __shared__ double sred[kVecBlock / 64], stot;
+  const int pr = find_job(J.prefix, J.n, blockIdx.x);
   const VecJob& v = J.jobs[pr];
   if (!ld_coherent(v.state + ST_ACTIVE)) return;
-  const int nb = J.prefix[pr + 1] - J.prefix[pr];
-  double a = 0.0, b = 0.0;
-  for (int i = threadIdx.x; i < nb; i += 256) {
-    a += v.red[2 * i];
-    b += v.red[2 * i + 1];
-  }
-  const double rr = block_sum<256>(a, sred);
-  const double rz = block_sum<256>(b, sred);
-  if (threadIdx.x == 0) {
+  const int lb = blockIdx.x - J.prefix[pr], nb = J.prefix[pr + 1] - J.prefix[pr];
+  const double rr = sum_parts(v.red, nb, sred, &stot);
+  __syncthreads();
+  const double rz = sum_parts(v.red + nb, nb, sred, &stot);
+  const double rz_old = ld_coherent(v.sc + SC_RZOLD), bb = ld_coherent(v.sc + SC_BB), rtol = ld_coherent(v.sc + SC_RTOL);
+  const int iters = ld_coherent(v.state + ST_NEXT), maxit = ld_coherent(v.state + ST_MAXIT);
+  const double beta = rz / rz_old, rel = sqrt(rr) / sqrt(bb);
+  const bool done = rel <= rtol || iters >= maxit;
+  if (lb == 0 && threadIdx.x == 0) {
     double* sc = v.sc;
     int* st = v.state;
-    const double rz_old = ld_coherent(sc + SC_RZ), bb = ld_coherent(sc + SC_BB), rtol = ld_coherent(sc + SC_RTOL);
-    const int iters = ld_coherent(st + ST_ITERS) + 1, maxit = ld_coherent(st + ST_MAXIT);
     sc[SC_RR] = rr;
     sc[SC_RZNEW] = rz;
-    sc[SC_BETA] = rz / rz_old;
+    sc[SC_BETA] = beta;
     sc[SC_RZ] = rz;
-    st[ST_ITERS] = iters;
-    const double rel = sqrt(rr) / sqrt(bb);
     sc[SC_RELRES] = rel;
-    if (rel <= rtol) {
-      st[ST_FLAG] = 0;
-      st[ST_ACTIVE] = 0;
-    } else if (iters >= maxit) {
-      st[ST_FLAG] = 1;
+    st[ST_ITERS] = iters;
+    if (done) {
+      st[ST_FLAG] = rel <= rtol ? 0 : 1;
       st[ST_ACTIVE] = 0;
     }
-    J.active_out[pr] = (rel <= rtol || iters >= maxit) ? 0 : 1;
+    J.active_out[pr] = done ? 0 : 1;
   }
+  if (done) return;
+  const float b = (float)beta;
+  for (int i = lb * kVecBlock + threadIdx.x; i < v.n3; i += nb * kVecBlock) v.p[i] = fmaf(b, v.p[i], v.z[i]);
 }
 
-hipError_t launch_pcg_beta_batch(const VecJobs& j, hipStream_t st) {
-  hipLaunchKernelGGL(pcg_beta_batch_kernel, dim3(j.n), dim3(256), 0, st, j);
+hipError_t launch_pcg_step_batch(const VecJobs& j, hipStream_t st) {
+  hipLaunchKernelGGL(pcg_step_batch_kernel, dim3(j.prefix[j.n]), dim3(kVecBlock), 0, st, j);
   return hipGetLastError();
 }
 
+// p = z + beta p with the beta of the flexible solve
 __global__ __launch_bounds__(kVecBlock) void pcg_direction_batch_kernel(const VecJobs J) {
   const int pr = find_job(J.prefix, J.n, blockIdx.x);
   const VecJob& v = J.jobs[pr];

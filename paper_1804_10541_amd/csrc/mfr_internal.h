@@ -250,7 +250,7 @@ struct AxpyJobs {
 // Conjugate-gradient vectors and device-side control of one problem.
 // ST_MAXIT and SC_RTOL are copied from the job table by the start kernel, so
 // launches captured once stay valid for later solves with other limits.
-enum PcgState : int { ST_ACTIVE = 0, ST_ITERS = 1, ST_FLAG = 2, ST_MAXIT = 3, ST_FALLBACK = 4, ST_COUNT = 5 };
+enum PcgState : int { ST_ACTIVE = 0, ST_ITERS = 1, ST_FLAG = 2, ST_MAXIT = 3, ST_FALLBACK = 4, ST_NEXT = 5, ST_COUNT = 6 };
 struct VecJob {
   float *r, *z, *p, *q, *s;
   const float* b;
@@ -307,7 +307,7 @@ hipError_t launch_h0_solve(const H0Tables& t, const float* v, float* x, float* t
 
 // PCG vector kernels.  sc: device scalars (see PcgSlot).
 enum PcgSlot : int {
-  SC_BB = 0, SC_RZ = 1, SC_PQ = 2, SC_RR = 3, SC_RZNEW = 4, SC_ALPHA = 5, SC_BETA = 6,
+  SC_BB = 0, SC_RZ = 1, SC_PQ = 2, SC_RR = 3, SC_RZNEW = 4, SC_ALPHA = 5, SC_BETA = 6, SC_RZOLD = 7,
   SC_D = 8, SC_S = 9, SC_J = 10, SC_DOT = 11, SC_RELRES = 12, SC_RTOL = 13, SC_ZR = 14, SC_ZRP = 15,
   SC_COUNT = 16
 };
@@ -346,7 +346,7 @@ hipError_t launch_dot_batch(const VecJobs& j, hipStream_t st);
 hipError_t launch_pcg_init_batch(const VecJobs& j, hipStream_t st);
 hipError_t launch_pcg_alpha_batch(const VecJobs& j, hipStream_t st);
 hipError_t launch_pcg_update_batch(const VecJobs& j, hipStream_t st);
-hipError_t launch_pcg_beta_batch(const VecJobs& j, hipStream_t st);
+hipError_t launch_pcg_step_batch(const VecJobs& j, hipStream_t st);
 hipError_t launch_pcg_direction_batch(const VecJobs& j, hipStream_t st);
 
 // ---- learned preconditioner (cnn_kernels.hip, pc_kernels.hip) ---------------------
