@@ -1002,14 +1002,18 @@ static hipError_t launch_tiles(const mfr_ctx* c, int mode, const TileParams& tp,
   return launch_tile(t.shape, mode, tp, u, p, t.grid(), c->stream);
 }
 
+// The tile and node-pass partials of an objective or gradient into sc[SC_D], sc[SC_S].
+static hipError_t sum_objective(mfr_ctx* c) {
+  static_assert(SC_S == SC_D + 1, "the two sums are neighbours");
+  return launch_sum2(c->red_tile, c->tiling.grid(), c->red_node, node_parts(c), c->sc + SC_D, c->stream);
+}
+
 // Enqueue: D and S sums into sc[SC_D], sc[SC_S].
 mfr_status enqueue_objective(mfr_ctx* c, const float* u) {
-  const Tiling& t = c->tiling;
   HIP_TRY(timed(c, 0, [&] { return launch_tiles(c, MODE_OBJ, c->tp, u, nullptr); }));
-  HIP_TRY(launch_sum(c->red_tile, t.grid(), c->sc + SC_D, c->stream));
   NodeParams q = c->np;
   HIP_TRY(timed(c, 4, [&] { return launch_node_pass(NP_S, q, u, nullptr, node_blocks(c), c->stream); }));
-  HIP_TRY(launch_sum(c->red_node, node_blocks(c), c->sc + SC_S, c->stream));
+  HIP_TRY(sum_objective(c));
   return MFR_OK;
 }
 
@@ -1028,13 +1032,11 @@ mfr_status read_objective(mfr_ctx* c, double* J, double* D, double* S) {
 }
 
 mfr_status enqueue_gradient(mfr_ctx* c, const float* u, float* g) {
-  const Tiling& t = c->tiling;
   HIP_TRY(timed(c, 1, [&] { return launch_tiles(c, MODE_GRAD, c->tp, u, nullptr); }));
-  HIP_TRY(launch_sum(c->red_tile, t.grid(), c->sc + SC_D, c->stream));
   NodeParams q = c->np;
   q.s_ngf = (float)c->geo.grad_scale();
   HIP_TRY(timed(c, 4, [&] { return launch_node_pass(NP_GRAD, q, u, g, node_blocks(c), c->stream); }));
-  HIP_TRY(launch_sum(c->red_node, node_parts(c), c->sc + SC_S, c->stream));
+  HIP_TRY(sum_objective(c));
   return MFR_OK;
 }
 
@@ -1519,9 +1521,8 @@ mfr_status mfr_gn_step_async(mfr_ctx* c, float* u, const mfr_gn_opts* o, double*
   for (int ls = 0; ls < o->armijo_max; ++ls) {
     HIP_TRY(launch_ls_trial(n3, u, (float)eta, dir, trial, search, c->stream));
     HIP_TRY(timed(c, 0, [&] { return launch_tiles(c, MODE_OBJ, tp, trial, nullptr); }));
-    HIP_TRY(launch_sum(c->red_tile, c->tiling.grid(), c->sc + SC_D, c->stream));
     HIP_TRY(timed(c, 4, [&] { return launch_node_pass(NP_S, q, trial, nullptr, node_blocks(c), c->stream); }));
-    HIP_TRY(launch_sum(c->red_node, node_blocks(c), c->sc + SC_S, c->stream));
+    HIP_TRY(sum_objective(c));
     HIP_TRY(launch_ls_check(c->sc + SC_D, dmul, smul, sk, alpha, o->armijo_c1, eta, ls, search, info, c->stream));
     eta *= 0.5;
   }

@@ -45,18 +45,24 @@ __device__ __forceinline__ int find_job(const int (&prefix)[N], int n, int item)
 }  // namespace
 
 // ---- per-problem fixed-order sums: one group per problem -------------------------
-__global__ __launch_bounds__(256) void sum_batch_kernel(const SumJobs J) {
-  __shared__ double sred[4];
+// (the order of launch_sum, so that both give the same bits)
+__global__ __launch_bounds__(1024) void sum_batch_kernel(const SumJobs J) {
+  __shared__ double sred[16];
   const SumJob& s = J.jobs[blockIdx.x];
   if (J.active && !ld_coherent(J.active + blockIdx.x)) return;
-  double a = 0.0;
-  for (int i = threadIdx.x; i < s.n; i += 256) a += s.parts[i * s.stride];
-  a = block_sum<256>(a, sred);
-  if (threadIdx.x == 0) *s.out = a;
+  double a[4] = {0.0, 0.0, 0.0, 0.0};
+  int i = threadIdx.x;
+  for (; i + 3 * 1024 < s.n; i += 4 * 1024) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) a[k] += s.parts[(i + k * 1024) * s.stride];
+  }
+  for (; i < s.n; i += 1024) a[0] += s.parts[i * s.stride];
+  const double t = block_sum<1024>((a[0] + a[1]) + (a[2] + a[3]), sred);
+  if (threadIdx.x == 0) *s.out = t;
 }
 
 hipError_t launch_sum_batch(const SumJobs& j, hipStream_t st) {
-  hipLaunchKernelGGL(sum_batch_kernel, dim3(j.n), dim3(256), 0, st, j);
+  hipLaunchKernelGGL(sum_batch_kernel, dim3(j.n), dim3(1024), 0, st, j);
   return hipGetLastError();
 }
 

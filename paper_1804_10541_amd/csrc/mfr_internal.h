@@ -277,6 +277,7 @@ hipError_t launch_tile_batch(const TileShape& s, int mode, const BatchJobs& j, i
 hipError_t launch_node_pass(int mode, const NodeParams& q, const float* f, float* out, int blocks,
                             hipStream_t st);
 hipError_t launch_sum(const double* parts, int n, double* out, hipStream_t st);
+hipError_t launch_sum2(const double* a, int na, const double* b, int nb, double* out, hipStream_t st);   // into out[0], out[1]
 // bz: zero border along z (2; 0 for a two-dimensional template, mz = 1)
 hipError_t launch_pad_template(const float* T, float* Tp, int mx, int my, int mz, int bz, hipStream_t st);
 // Two-dimensional problems (plane_tile.hip): the fused tile kernel and the exact

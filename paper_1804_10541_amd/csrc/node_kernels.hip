@@ -348,18 +348,42 @@ hipError_t launch_node_pass(int mode, const NodeParams& q, const float* f, float
   return launch_node_mode<NP_HV>(q, f, out, blocks, st);
 }
 
-// Fixed-order sum of n float64 partials by one work-group.
-__global__ __launch_bounds__(256) void sum_kernel(const double* __restrict__ parts, int n,
-                                                  double* __restrict__ out) {
-  __shared__ double sred[4];
-  double s = 0.0;
-  for (int i = threadIdx.x; i < n; i += 256) s += parts[i];
-  s = block_sum<256>(s, sred);
+// Fixed-order sum of n float64 partials by one work-group: four running sums per
+// thread, so that a thread's loads do not wait for each other (16,000 partials of a
+// 4096 x 4096 problem: 17.7 us with 256 threads and one sum each).
+__device__ __forceinline__ double sum_group(const double* __restrict__ parts, int n, double* sred) {
+  double s[4] = {0.0, 0.0, 0.0, 0.0};
+  int i = threadIdx.x;
+  for (; i + 3 * 1024 < n; i += 4 * 1024) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) s[k] += parts[i + k * 1024];
+  }
+  for (; i < n; i += 1024) s[0] += parts[i];
+  return block_sum<1024>((s[0] + s[1]) + (s[2] + s[3]), sred);
+}
+
+__global__ __launch_bounds__(1024) void sum_kernel(const double* __restrict__ parts, int n,
+                                                   double* __restrict__ out) {
+  __shared__ double sred[16];
+  const double s = sum_group(parts, n, sred);
   if (threadIdx.x == 0) *out = s;
 }
 
+// Two sums in one launch: a into out[0], b into out[1].
+__global__ __launch_bounds__(1024) void sum2_kernel(const double* __restrict__ a, int na, const double* __restrict__ b,
+                                                    int nb, double* __restrict__ out) {
+  __shared__ double sred[16];
+  const double s = blockIdx.x == 0 ? sum_group(a, na, sred) : sum_group(b, nb, sred);
+  if (threadIdx.x == 0) out[blockIdx.x] = s;
+}
+
 hipError_t launch_sum(const double* parts, int n, double* out, hipStream_t st) {
-  hipLaunchKernelGGL(sum_kernel, dim3(1), dim3(256), 0, st, parts, n, out);
+  hipLaunchKernelGGL(sum_kernel, dim3(1), dim3(1024), 0, st, parts, n, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_sum2(const double* a, int na, const double* b, int nb, double* out, hipStream_t st) {
+  hipLaunchKernelGGL(sum2_kernel, dim3(2), dim3(1024), 0, st, a, na, b, nb, out);
   return hipGetLastError();
 }
 
