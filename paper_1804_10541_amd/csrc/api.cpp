@@ -1324,7 +1324,7 @@ mfr_status mfr_create(const mfr_grid* grid, void* hip_stream, void* workspace, s
 }
 
 void mfr_destroy(mfr_ctx* ctx) {
-  // pending copies may still read host memory the context owns
+  // work in flight may still use memory that the context or its caller gives back
   if (ctx) (void)hipStreamSynchronize(ctx->stream);
   if (ctx)
     for (mfr_pc* pc : ctx->bound_pcs) pc_release_context(pc);

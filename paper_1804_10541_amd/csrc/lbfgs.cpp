@@ -59,44 +59,18 @@ mfr_status check_geo(const Geo& g) {
   return MFR_OK;
 }
 
-// Orthonormal DCT-II matrices, their transposes and the eigenvalues
-// -4 sin^2(pi k / 2n) / hy^2 of the Neumann second difference, built once per
-// context on the host and copied into work (the work buffer is the caller's,
-// so every call copies them again; the host copies outlive the copies).
-mfr_status upload_tables(mfr_ctx* c, const LbLayout& L, char* work, H0Tables* t) {
+// Cosine matrices and eigenvalues of the Neumann second difference into work (the
+// buffer is the caller's, so every call forms them again, on the device).
+mfr_status make_tables(mfr_ctx* c, const LbLayout& L, char* work, H0Tables* t) {
   const Geo& g = c->geo;
-  if (c->h0_lam.empty()) {
-    for (int d = 0; d < 3; ++d) {
-      const int n = g.n[d];
-      std::vector<float>& C = c->h0_C[d];
-      std::vector<float>& Ct = c->h0_Ct[d];
-      C.assign((size_t)n * n, 0.0f);
-      Ct.assign((size_t)n * n, 0.0f);
-      for (int k = 0; k < n; ++k) {
-        const double w = std::sqrt((k == 0 ? 1.0 : 2.0) / n);
-        for (int i = 0; i < n; ++i) {
-          const float v = (float)(w * std::cos(M_PI * k * (2.0 * i + 1.0) / (2.0 * n)));
-          C[(size_t)k * n + i] = v;
-          Ct[(size_t)i * n + k] = v;
-        }
-        const double sn = std::sin(M_PI * k / (2.0 * n));
-        c->h0_lam.push_back((float)(-4.0 * sn * sn / (g.hy[d] * g.hy[d])));
-      }
-    }
-  }
   for (int d = 0; d < 3; ++d) {
-    HIP_TRY(hipMemcpyAsync(work + L.C[d], c->h0_C[d].data(), sizeof(float) * c->h0_C[d].size(),
-                           hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(hipMemcpyAsync(work + L.Ct[d], c->h0_Ct[d].data(), sizeof(float) * c->h0_Ct[d].size(),
-                           hipMemcpyHostToDevice, c->stream));
     t->n[d] = g.n[d];
     t->C[d] = reinterpret_cast<const float*>(work + L.C[d]);
     t->Ct[d] = reinterpret_cast<const float*>(work + L.Ct[d]);
   }
-  HIP_TRY(hipMemcpyAsync(work + L.lam, c->h0_lam.data(), sizeof(float) * c->h0_lam.size(), hipMemcpyHostToDevice,
-                         c->stream));
   t->lam = reinterpret_cast<const float*>(work + L.lam);
   t->nc = g.nc();
+  HIP_TRY(launch_h0_tables(*t, g.hy, c->stream));
   return MFR_OK;
 }
 
@@ -129,7 +103,7 @@ mfr_status lbfgs_run(mfr_ctx* c, float* u, const mfr_lbfgs_opts* o, char* work, 
   const auto t0 = std::chrono::steady_clock::now();
   const int n3 = (int)(c->geo.nc() * c->geo.nbar);
   H0Tables tab{};
-  MFR_TRY(upload_tables(c, L, work, &tab));
+  MFR_TRY(make_tables(c, L, work, &tab));
   auto vec = [&](int k) { return reinterpret_cast<float*>(work + L.vec + (size_t)k * L.vbytes); };
   float* ta = vec(0);
   float* tb = vec(1);
@@ -257,7 +231,7 @@ mfr_status mfr_h0_solve(mfr_ctx* c, double gamma, const float* v, float* x, void
   MFR_TRY(check_work(c, L, work, work_bytes));
   char* w = static_cast<char*>(work);
   H0Tables tab{};
-  MFR_TRY(upload_tables(c, L, w, &tab));
+  MFR_TRY(make_tables(c, L, w, &tab));
   float* ta = reinterpret_cast<float*>(w + L.vec);
   float* tb = reinterpret_cast<float*>(w + L.vec + L.vbytes);
   float c2 = 0.0f, c1 = 0.0f;

@@ -290,9 +290,10 @@ hipError_t launch_jacobi_tile(const JacParams& j, const float* u, float* diag, h
 hipError_t launch_diag_tile(const DiagTileParams& d, const float* u, float* diag, hipStream_t st);
 constexpr int kJacAX = 32, kJacAY = 32;   // voxel columns covered by one Jacobi work-group
 
-// L-BFGS initial-matrix solve (lbfgs_kernels.hip): orthonormal DCT-II matrices
-// C[d] (n_d x n_d, row k = cosine k), their transposes Ct[d], and the per-axis
+// L-BFGS initial-matrix solve (lbfgs_kernels.hip): cosine matrices C[d] of the
+// axes (even and odd half-size ones), their transposes Ct[d], and the per-axis
 // eigenvalues of the Neumann second difference (lam: x, then y, then z).
+constexpr int kH0Half = 128;   // most rows of a half-size matrix that one group covers
 struct H0Tables {
   int n[3];
   int nc;   // components (3; 2 for a two-dimensional problem, n[2] = 1)
@@ -300,6 +301,8 @@ struct H0Tables {
   const float* Ct[3];
   const float* lam;
 };
+// Fills the tables of t (node spacings hy) on the device.
+hipError_t launch_h0_tables(const H0Tables& t, const double hy[3], hipStream_t st);
 // x = (c2 L^T L + c1 L + gamma I)^{-1} v per component (L diagonal in the cosine
 // basis with eigenvalue lx + ly + lz); ta, tb: scratch node vectors (x may
 // alias v, not ta or tb).
