@@ -231,7 +231,7 @@ static int most_chunks(const std::vector<Conv1>& c, int n, int len) {
 
 // Chunks of a march over `planes` planes by xy column blocks, each chunk costing
 // its planes plus `lead` planes of lead-in: the number of chunks (of min_len to
-// kMaxChunk planes) with the least estimated time on 256 CUs.  A CU holds per_cu
+// max_len planes) with the least estimated time on 256 CUs.  A CU holds per_cu
 // groups at once; where it holds a single one of two, that one advances
 // faster, by solo.  Rounds of 256 per_cu groups follow each other; a last round
 // of at most one group per CU costs solo of a full one.  Measured with the
@@ -240,11 +240,11 @@ static int most_chunks(const std::vector<Conv1>& c, int n, int len) {
 // of 16 at 128x128x96 49 -> 38 us, 8 of 4 instead of 2 of 16 at 32^3 35 -> 17 us
 // (short chunks leave fewer planes to march one after the other; where the chip
 // is full they only add lead-in planes).
-static int pick_chunks(long long xy, int planes, int min_len, int per_cu, double lead, double solo) {
+static int pick_chunks(long long xy, int planes, int min_len, int max_len, int per_cu, double lead, double solo) {
   const long long slots = 256LL * per_cu;
   int best = 1;
   double best_t = 0.0;
-  for (int c = (planes + kMaxChunk - 1) / kMaxChunk; c <= std::max(1, planes / min_len); ++c) {
+  for (int c = (planes + max_len - 1) / max_len; c <= std::max(1, planes / min_len); ++c) {
     const int len = (planes + c - 1) / c;
     const long long groups = xy * ((planes + len - 1) / len);
     const long long full = groups / slots, rem = groups % slots;
@@ -264,6 +264,24 @@ static int min_chunk(const std::vector<Conv1>& c, int n) {
   int len = 4;
   while (len < (int)c.size() && most_chunks(c, n, len) > 2) ++len;
   return len;
+}
+
+// Whether no voxel of the axis skips a cell to a neighbour and, for `one`, none has
+// both neighbours in other cells.
+static bool cells_follow(const std::vector<Conv1>& c, bool one) {
+  for (size_t i = 0; i < c.size(); ++i) {
+    const int dm = i > 0 ? c[i].n0 - c[i - 1].n0 : 0, dp = i + 1 < c.size() ? c[i + 1].n0 - c[i].n0 : 0;
+    if (dm < 0 || dm > 1 || dp < 0 || dp > 1 || (one && dm && dp)) return false;
+  }
+  return true;
+}
+
+// Whether every conversion weight of the axis is at least 2^-12, so that a row's
+// entries may be summed divided by them.
+static bool weights_clear(const std::vector<Conv1>& c) {
+  for (const Conv1& e : c)
+    if (!(e.f >= 1.0f / 4096.0f && e.f <= 1.0f - 1.0f / 4096.0f)) return false;
+  return true;
 }
 
 static Tiling make_tiling_plane(const Geo& g, const std::vector<Conv1>& cx, const std::vector<Conv1>& cy) {
@@ -309,7 +327,36 @@ static Tiling make_tiling_plane(const Geo& g, const std::vector<Conv1>& cx, cons
     d.nyt = std::max(d.nyt, cy[std::min(ye, g.m[1] - 1)].n0 + 2 - cy[std::max(yb - 1, 0)].n0);
   }
   d.on = g.n[0] <= g.m[0] + 1 && g.n[1] <= g.m[1] + 1 && d.nxt <= kPlaneNT - 32;
+  d.march = 0;
+  t.dgn = d;
   return t;
+}
+
+// kDiagBX x kDiagBY groups in the given number of chunks of at most `longest` planes;
+// a group's z node block spans the planes its rows' z stencils reach.
+static DiagTiling diag_tiling(const Geo& g, const std::vector<Conv1>& cx, const std::vector<Conv1>& cy,
+                              const std::vector<Conv1>& cz, int chunks, int longest) {
+  DiagTiling d{};
+  const int DX = kDiagBX - 2, DY = kDiagBY - 2;
+  d.tiles_x = (g.m[0] + DX - 1) / DX;
+  d.tiles_y = (g.m[1] + DY - 1) / DY;
+  d.chunk_len = std::min(std::min((g.m[2] + chunks - 1) / chunks, g.m[2]), longest);
+  d.chunks = (g.m[2] + d.chunk_len - 1) / d.chunk_len;
+  for (int i = 0; i < d.tiles_x; ++i) {
+    const int a0 = std::max(i * DX - 1, 0), a1 = std::min(i * DX + DX, g.m[0] - 1);
+    d.nxt = std::max(d.nxt, cx[a1].n0 + 2 - cx[a0].n0);
+  }
+  for (int i = 0; i < d.tiles_y; ++i) {
+    const int a0 = std::max(i * DY - 1, 0), a1 = std::min(i * DY + DY, g.m[1] - 1);
+    d.nyt = std::max(d.nyt, cy[a1].n0 + 2 - cy[a0].n0);
+  }
+  for (int i = 0; i < d.chunks; ++i) {
+    const int zb = i * d.chunk_len, ze = std::min(zb + d.chunk_len, g.m[2]);
+    d.nzt = std::max(d.nzt, cz[std::min(ze, g.m[2] - 1)].n0 + 2 - cz[std::max(zb - 1, 0)].n0);
+  }
+  d.on = g.n[0] <= g.m[0] + 1 && g.n[1] <= g.m[1] + 1 && g.n[2] <= g.m[2] + 1 && d.nxt <= kDiagBX + 1 &&
+         d.nyt <= kDiagBY + 1 && d.nxt * d.nyt <= kDiagBX * kDiagBY / 2;
+  return d;
 }
 
 Tiling make_tiling(const Geo& g, const std::vector<Conv1>& cx, const std::vector<Conv1>& cy,
@@ -328,7 +375,7 @@ Tiling make_tiling(const Geo& g, const std::vector<Conv1>& cx, const std::vector
     const int target = cfg.target_groups > 0 ? cfg.target_groups : 2048;
     chunks = std::min(std::max(1, (target + xy - 1) / xy), std::max(1, g.m[2] / 16));
   } else {
-    chunks = pick_chunks(xy, g.m[2], minc, t.shape.bx * t.shape.by > 512 ? 1 : 2, 4.0, 0.7);
+    chunks = pick_chunks(xy, g.m[2], minc, kMaxChunk, t.shape.bx * t.shape.by > 512 ? 1 : 2, 4.0, 0.7);
   }
   int clen = (g.m[2] + chunks - 1) / chunks;
   if (cfg.chunk_len > 0) clen = cfg.chunk_len;
@@ -351,33 +398,21 @@ Tiling make_tiling(const Geo& g, const std::vector<Conv1>& cx, const std::vector
   t.smx = most_groups(cx, g.n[0], TX, t.tiles_x);
   t.smy = most_groups(cy, g.n[1], TY, t.tiles_y);
   t.smz = most_chunks(cz, g.n[2], t.chunk_len);
-  // the diagonal's own tiling (two groups per CU, two planes of lead-in and one
+  // The diagonal's own tiling (two groups per CU, two planes of lead-in and one
   // node plane more to write): its march is bound by instruction issue sooner, so
-  // a single group on a CU gains less (solo 0.8); a group's z node block spans the planes its rows' z stencils reach
-  DiagTiling& d = t.dg;
+  // a single group on a CU gains less (solo 0.8).
   const int DX = kDiagBX - 2, DY = kDiagBY - 2;
-  d.tiles_x = (g.m[0] + DX - 1) / DX;
-  d.tiles_y = (g.m[1] + DY - 1) / DY;
-  const int dxy = d.tiles_x * d.tiles_y;
-  const int dch = compact ? std::min(std::max(1, (4096 + dxy - 1) / dxy), std::max(1, g.m[2] / 16))
-                          : pick_chunks(dxy, g.m[2], minc, 2, 3.0, 0.8);
-  d.chunk_len = std::min(std::min((g.m[2] + dch - 1) / dch, g.m[2]), kMaxChunk);
-  d.chunks = (g.m[2] + d.chunk_len - 1) / d.chunk_len;
-  d.nxt = d.nyt = d.nzt = 0;
-  for (int i = 0; i < d.tiles_x; ++i) {
-    const int a0 = std::max(i * DX - 1, 0), a1 = std::min(i * DX + DX, g.m[0] - 1);
-    d.nxt = std::max(d.nxt, cx[a1].n0 + 2 - cx[a0].n0);
+  const int dxy = ((g.m[0] + DX - 1) / DX) * ((g.m[1] + DY - 1) / DY);
+  const bool follow = cells_follow(cx, true) && cells_follow(cy, true) && cells_follow(cz, false);
+  t.dgn = diag_tiling(g, cx, cy, cz, std::min(std::max(1, (4096 + dxy - 1) / dxy), std::max(1, g.m[2] / 16)), kMaxChunk);
+  t.dg = t.dgn;
+  if (!compact) {
+    const int longest = follow ? kMarchChunk : kMaxChunk;
+    t.dg = diag_tiling(g, cx, cy, cz, pick_chunks(dxy, g.m[2], minc, longest, 2, 3.0, 0.8), longest);
   }
-  for (int i = 0; i < d.tiles_y; ++i) {
-    const int a0 = std::max(i * DY - 1, 0), a1 = std::min(i * DY + DY, g.m[1] - 1);
-    d.nyt = std::max(d.nyt, cy[a1].n0 + 2 - cy[a0].n0);
-  }
-  for (int i = 0; i < d.chunks; ++i) {
-    const int zb = i * d.chunk_len, ze = std::min(zb + d.chunk_len, g.m[2]);
-    d.nzt = std::max(d.nzt, cz[std::min(ze, g.m[2] - 1)].n0 + 2 - cz[std::max(zb - 1, 0)].n0);
-  }
-  d.on = g.n[0] <= g.m[0] + 1 && g.n[1] <= g.m[1] + 1 && g.n[2] <= g.m[2] + 1 &&
-         d.nxt <= kDiagBX + 1 && d.nyt <= kDiagBY + 1 && d.nxt * d.nyt <= kDiagBX * kDiagBY / 2;
+  DiagTiling& d = t.dg;
+  if (d.on && follow && d.nxt <= kMarchNX && d.nyt <= kMarchNY && d.chunk_len <= kMarchChunk)
+    d.march = weights_clear(cx) && weights_clear(cy) ? 2 : 1;
   return t;
 }
 
@@ -433,7 +468,10 @@ Layout make_layout(const Geo& g, const Tiling& t) {
   L.dorgx = take(dg.on ? sizeof(int) * dg.tiles_x : 0);
   L.dorgy = take(dg.on ? sizeof(int) * dg.tiles_y : 0);
   L.dorgz = take(dg.on ? sizeof(int) * dg.chunks : 0);
-  L.dpart = take(dg.on ? sizeof(float) * (size_t)dg.grid() * 3 * dg.nzt * dg.nyt * dg.nxt : 0);
+  // (one diagonal at a time on the context's stream: both tilings share the blocks)
+  L.nntz = take(t.dgn.on ? sizeof(Range1) * g.n[2] : 0);
+  L.norgz = take(t.dgn.on ? sizeof(int) * t.dgn.chunks : 0);
+  L.dpart = take(sizeof(float) * std::max(dg.floats(), t.dgn.floats()));
   L.red_tile = take(sizeof(double) * (size_t)t.grid());
   // node-pass partials (one per group) and those of the other vector kernels
   L.red_node = take(sizeof(double) * std::max(node_groups(g.nbar), 2 * 1024));
@@ -740,41 +778,41 @@ mfr_status ctx_init(mfr_ctx* c, const mfr_grid* grid, void* stream, void* ws, si
   // voxel-tiled diagonal: the groups and chunks holding each node, the first
   // node of each group's block (z: the planes its rows' z stencils reach)
   const DiagTiling& dg = t.dg;
-  std::vector<Range1> dntx, dnty, dntz;
-  std::vector<int> dorgx, dorgy, dorgz;
+  std::vector<Range1> dntx, dnty, dntz, nntz;
+  std::vector<int> dorgx, dorgy, dorgz, norgz;
   if (dg.on) {
     const int DX = kDiagBX - 2, DY = kDiagBY - 2;
     dntx.resize(g.n[0]);
     dnty.resize(g.n[1]);
-    dntz.resize(g.n[2]);
     dorgx.resize(dg.tiles_x);
     dorgy.resize(dg.tiles_y);
-    dorgz.resize(dg.chunks);
-    std::vector<int> dzend(dg.chunks);
     for (int i = 0; i < g.n[0]; ++i) dntx[i] = groups_touching(colx[i], DX, dg.tiles_x);
     for (int i = 0; i < g.n[1]; ++i) dnty[i] = groups_touching(coly[i], DY, dg.tiles_y);
     for (int i = 0; i < dg.tiles_x; ++i) dorgx[i] = cx[std::max(i * DX - 1, 0)].n0;
     for (int i = 0; i < dg.tiles_y; ++i) dorgy[i] = cy[std::max(i * DY - 1, 0)].n0;
-    for (int i = 0; i < dg.chunks; ++i) {
-      const int zb = i * dg.chunk_len, ze = std::min(zb + dg.chunk_len, g.m[2]);
-      dorgz[i] = cz[std::max(zb - 1, 0)].n0;
-      dzend[i] = cz[std::min(ze, g.m[2] - 1)].n0 + 2;
-    }
-    for (int k = 0; k < g.n[2]; ++k) {   // the chunks whose blocks hold node plane k (contiguous)
-      int lo = dg.chunks, hi = -1;
-      for (int i = 0; i < dg.chunks; ++i)
-        if (dorgz[i] <= k && k < dzend[i]) {
-          lo = std::min(lo, i);
-          hi = std::max(hi, i);
+    // the chunks whose blocks hold each node plane (contiguous) and their first node planes
+    auto planes = [&](const DiagTiling& q, std::vector<Range1>& ntz, std::vector<int>& orgz) {
+      ntz.assign(g.n[2], Range1{q.chunks, -1});
+      orgz.resize(q.chunks);
+      for (int i = 0; i < q.chunks; ++i) {
+        const int zb = i * q.chunk_len, ze = std::min(zb + q.chunk_len, g.m[2]);
+        orgz[i] = cz[std::max(zb - 1, 0)].n0;
+        for (int k = orgz[i]; k < cz[std::min(ze, g.m[2] - 1)].n0 + 2; ++k) {
+          ntz[k].lo = std::min(ntz[k].lo, i);
+          ntz[k].hi = std::max(ntz[k].hi, i);
         }
-      dntz[k] = Range1{lo, hi};
-    }
+      }
+    };
+    planes(dg, dntz, dorgz);
+    planes(t.dgn, nntz, norgz);
     HIP_TRY(up(L.dntx, dntx.data(), sizeof(Range1) * dntx.size()));
     HIP_TRY(up(L.dnty, dnty.data(), sizeof(Range1) * dnty.size()));
     HIP_TRY(up(L.dntz, dntz.data(), sizeof(Range1) * dntz.size()));
     HIP_TRY(up(L.dorgx, dorgx.data(), sizeof(int) * dorgx.size()));
     HIP_TRY(up(L.dorgy, dorgy.data(), sizeof(int) * dorgy.size()));
     HIP_TRY(up(L.dorgz, dorgz.data(), sizeof(int) * dorgz.size()));
+    HIP_TRY(up(L.nntz, nntz.data(), sizeof(Range1) * nntz.size()));
+    HIP_TRY(up(L.norgz, norgz.data(), sizeof(int) * norgz.size()));
   }
   HIP_TRY(hipStreamSynchronize(c->stream));
 
@@ -902,6 +940,7 @@ mfr_status ctx_init(mfr_ctx* c, const mfr_grid* grid, void* stream, void* ws, si
   dt.t.nxt = dg.nxt;
   dt.t.nyt = dg.nyt;
   dt.t.nzt = dg.nzt;
+  dt.march = dg.march;
   dt.t.part = at<float>(c->ws, L.dpart);
   dt.t.red = nullptr;
   dt.rx = d.rx;
@@ -917,6 +956,14 @@ mfr_status ctx_init(mfr_ctx* c, const mfr_grid* grid, void* stream, void* ws, si
   dt.ihy2x = d.ihy2x;
   dt.ihy2y = d.ihy2y;
   dt.ihy2z = d.ihy2z;
+
+  c->dtn = dt;
+  c->dtn.march = 0;
+  c->dtn.t.chunks = t.dgn.chunks;
+  c->dtn.t.chunk_len = t.dgn.chunk_len;
+  c->dtn.t.nzt = t.dgn.nzt;
+  c->dtn.ntz = at<Range1>(c->ws, L.nntz);
+  c->dtn.orgz = at<int>(c->ws, L.norgz);
 
   c->sc = at<double>(c->ws, L.sc);
   c->red_tile = p.red;
@@ -970,6 +1017,15 @@ hipError_t enqueue_diag(mfr_ctx* c, const float* u, float* diag) {
   if (c->tiling.dg.on) return launch_diag_tile(c->dtp, u, diag, c->stream);
   if (c->jac_tiled) return launch_jacobi_tile(c->jp, u, diag, c->stream);
   return launch_jacobi_diag(c->dp, u, diag, c->stream);
+}
+
+// The diagonal as input of the learned preconditioner, summed in one order whatever
+// kernel and split are taken for the diagonal itself: the network rounds its inputs
+// to 16 bits, so a last bit of a sum can change an activation by 2^-9 (outputs 2e-3
+// of their size apart with another z split alone, on half of the inputs tried).
+hipError_t enqueue_diag_network(mfr_ctx* c, const float* u, float* diag) {
+  if (c->geo.dim == 2 || !c->tiling.dg.on) return enqueue_diag(c, u, diag);
+  return launch_diag_tile(c->dtn, u, diag, c->stream);
 }
 
 // The Jacobi preconditioner of a CG solve: the exact diagonal with zero entries
@@ -1343,6 +1399,7 @@ mfr_status mfr_set_images(mfr_ctx* c, const float* R, const float* T) {
   c->dp.t.R = R;
   c->jp.t.R = R;
   c->dtp.t.R = R;
+  c->dtn.t.R = R;
   c->have_images = true;
   ++c->image_version;
   return MFR_OK;

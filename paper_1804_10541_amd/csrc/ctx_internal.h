@@ -75,11 +75,15 @@ std::vector<Conv1> prolong_table(int nf, double hyf, int nc, double hyc);
 // Tiling of the voxel-tiled Jacobi diagonal (kDiagBX x kDiagBY groups, its own
 // chunks); `on` when the node grid fits its per-group tables (at most one node
 // per voxel along each axis, at most half a group's threads of node columns).
+// `march`: every voxel has at most one x and one y neighbour in another cell and no
+// plane skips a node plane, so each column's sums stay in its thread's registers.
 struct DiagTiling {
   bool on;
+  int march;   // 0: no; 1: yes; 2: and every weight in x and y is at least 2^-12
   int tiles_x, tiles_y, chunks, chunk_len;
   int nxt, nyt, nzt;
   int grid() const { return tiles_x * tiles_y * chunks; }
+  size_t floats() const { return on ? (size_t)grid() * 3 * nzt * nyt * nxt : 0; }
 };
 
 struct Tiling {
@@ -87,7 +91,8 @@ struct Tiling {
   int tiles_x, tiles_y, chunks, chunk_len;
   int nxt, nyt, nzt;
   int smx, smy, smz;   // partial slots per axis: the most groups overlapping one node along it
-  DiagTiling dg;
+  DiagTiling dg;    // the diagonal
+  DiagTiling dgn;   // the diagonal in one order of summation: chunks of at least 16 planes, no march
   int grid() const { return tiles_x * tiles_y * chunks; }
 };
 
@@ -102,7 +107,7 @@ void set_tile_config(const mfr_tile_config& c);
 struct Layout {
   size_t Tp, cx, cy, cz, sx, sy, sz, ntx, nty, ntz, rx, ry, rz;
   size_t part, red_tile, red_node, red_vec, sc, vec, jbx, jby, jbz, ctrl, div;
-  size_t dntx, dnty, dntz, dorgx, dorgy, dorgz, dpart;   // voxel-tiled diagonal
+  size_t dntx, dnty, dntz, dorgx, dorgy, dorgz, nntz, norgz, dpart;   // voxel-tiled diagonal
   size_t total;
 };
 
@@ -140,7 +145,7 @@ struct mfr_ctx {
   mfr::NodeParams np;
   mfr::DiagParams dp;
   mfr::JacParams jp;
-  mfr::DiagTileParams dtp;
+  mfr::DiagTileParams dtp, dtn;   // the diagonal; the same in one order of summation
   bool jac_tiled;
   double* sc;
   double* red_tile;
@@ -208,6 +213,7 @@ hipError_t timed(mfr_ctx* c, int slot, F&& launch) {
 }
 
 hipError_t enqueue_diag(mfr_ctx* c, const float* u, float* diag);
+hipError_t enqueue_diag_network(mfr_ctx* c, const float* u, float* diag);
 hipError_t enqueue_pcg_diag(mfr_ctx* c, const float* u, float* diag);   // zero entries -> 1
 int node_blocks(const mfr_ctx* c);   // work-groups of a node pass
 int node_parts(const mfr_ctx* c);    // float64 partials of a gradient / Hv node pass (one per group)

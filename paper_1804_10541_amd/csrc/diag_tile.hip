@@ -465,6 +465,515 @@ __global__ __launch_bounds__(kDiagBX* kDiagBY) __attribute__((amdgpu_waves_per_e
   while (kflush < nzend) flush();
 }
 
+// ---- the diagonal on grids with at least two voxels per cell in x and y -----------
+
+namespace {
+
+// Local columns (rows) of a group by the node (of the group's block) they reach:
+// those of the cell left of it [lo1, hi1), those of the cell right of it [lo0, hi0),
+// and the two that reach it through their x (y) neighbour in the next cell only: e1
+// (the last column of the cell before lo1, weight w1 of its right neighbour) and e2
+// (the first one behind hi0, weight w2 of its left neighbour); -1: none.
+struct NodeCols {
+  int lo1, hi1, lo0, hi0, e1, e2;
+  float w1, w2;
+};
+
+template <bool SSD>
+struct MarchSmem {
+  static constexpr int BX = kDiagBX, BY = kDiagBY, NT = BX * BY;
+  static constexpr int MAXNX = kMarchNX, MAXNY = kMarchNY;
+  static constexpr int XP = SSD ? 0 : BX, NX = SSD ? 1 : NT + 2 * BX;
+  // a finished node plane per column (NGF: the four node columns of its cell, 2 i + j,
+  // of component d at 4 d, then the sums of the x and of the y neighbours' products;
+  // SSD: one sum per component) and its sums over x per row and node column
+  static constexpr int NB = SSD ? 3 : 18, NCC = SSD ? 3 : 9, BP = BX - 1, NO = (BY - 2) * BP;   // own columns only
+  float sTw[2][NX];
+  float sR[2][NX];
+  float sG[2][3][NX];
+  float sB[NB][NO];
+  float sC[NCC][BY - 2][MAXNX + 1];
+  float sCarry[SSD ? 1 : 3][SSD ? 1 : NT];
+  struct Axis {
+    float4 w;   // weights of the cell's node columns at the neighbours: (-, 0), (-, 1), (+, 0), (+, 1)
+    Samp1 s;
+    unsigned r;   // byte offset of the column (row) in a plane of the reference
+    float f;      // conversion fraction
+  } sAx[BX], sAy[BY];
+  NodeCols sNx[MAXNX], sNy[MAXNY];
+  Conv1 sCx[BX], sCy[BY];
+  Conv1 sCz[kMarchChunk + 4];
+  Samp1 sSz[kMarchChunk + 4];
+  float4 sZw[SSD ? 1 : kMarchChunk + 4];   // as Axis::w, for the planes
+};
+
+__device__ __forceinline__ NodeCols node_columns(const Conv1* c, int B, int first, int m, int node) {
+  // own columns first + 1 .. first + B - 2 (local l is column first + l) inside the image
+  NodeCols r{0, 0, 0, 0, -1, -1, 0.f, 0.f};
+  for (int l = 1; l < B - 1 && first + l < m; ++l) {
+    const int n = c[l].n0;
+    if (n == node - 1) {
+      if (r.hi1 == 0) r.lo1 = l;
+      r.hi1 = l + 1;
+    }
+    if (n == node) {
+      if (r.hi0 == 0) r.lo0 = l;
+      r.hi0 = l + 1;
+    }
+    if (n == node - 2 && first + l + 1 < m && c[l + 1].n0 == node - 1) {
+      r.e1 = l;
+      r.w1 = c[l + 1].f;
+    }
+    if (n == node + 1 && first + l > 0 && c[l - 1].n0 == node) {
+      r.e2 = l;
+      r.w2 = 1.0f - c[l - 1].f;
+    }
+  }
+  return r;
+}
+
+}  // namespace
+
+// The same partial node blocks where every cell has at least two voxels in x and y
+// and no plane skips a node plane in z (the host checks the tables): each column then
+// has at most one x and one y neighbour in another cell, so the thread of a column
+// keeps the squares of its rows for the 2 x 2 node columns of its cell in registers
+// over the march, with the products of its row straight from the exchange arrays.
+// With U_i = sum over (0, -x, +x), V_j = sum over (-y, +y) of product times weight
+// the row's entry for node column (i, j) and node plane q is
+//   wz_q (v_j U_i + w_i V_j) + w_i v_j (product -z and +z times their weights);
+// SCALED (no weight near 0) sums it divided by w_i v_j, which is applied once per
+// node plane: 32 instead of 46 operations per component.  No division by a weight
+// below 2^-12: voxels that close to a node take the other form.
+// The node column beyond the cell's edge gets the neighbour's product alone
+// (wz_q^2 c^2 is summed, the weights of x and y are applied once).  A finished node
+// plane is summed over the columns of each node in two fixed-order steps through
+// LDS.  Against the gather of 21 products by each of the five to six node columns
+// that a row reaches: a third of the operations and one barrier per plane.
+// Everything that a thread needs rarely is read from LDS, so that 128 registers
+// (two groups per CU) hold the rest: a spilled value would wait for the template
+// loads in flight (six of them cost 636 -> 524 us below).
+//
+// Bound by vector-instruction issue (about 340 per row plane and wave).  The
+// diagonal with its node pass, gather -> march (NGF; SSD): 512x512x128 voxels,
+// 129x129x33 nodes 894 -> 523 us (SSD 480 -> 207), 257x257x65 nodes 1290 -> 815 us,
+// 128x128x96, 65x65x49 nodes 97 -> 72 us.
+template <bool SSD, bool SCALED>
+__global__ __launch_bounds__(kDiagBX* kDiagBY) __attribute__((amdgpu_waves_per_eu(4))) void diag_march_kernel(
+    const DiagTileParams D, const float* __restrict__ u) {
+  using Sm = MarchSmem<SSD>;
+  constexpr int BX = Sm::BX, BY = Sm::BY, NT = Sm::NT, XP = Sm::XP, BP = Sm::BP;
+  constexpr int TX = BX - 2, TY = BY - 2;
+  __shared__ Sm S;
+  const TileParams& P = D.t;
+
+  const int tid = threadIdx.x;
+  const int tx = tid % BX, ty = tid / BX;
+  const int bid = xcd_block_id();
+  const int tile_x = bid % P.tiles_x;
+  const int rest = bid / P.tiles_x;
+  const int tile_y = rest % P.tiles_y;
+  const int chunk = rest / P.tiles_y;
+  const int x0 = tile_x * TX, y0 = tile_y * TY;
+  const int zb = chunk * P.chunk_len;
+  const int ze = min(P.mz, zb + P.chunk_len);
+
+  const int gx = x0 - 1 + tx, gy = y0 - 1 + ty;
+  const int cxi = min(max(gx, 0), P.mx - 1), cyi = min(max(gy, 0), P.my - 1);
+  // (opaque, so that no LDS address formed of it is kept in registers over the march)
+  auto opaque_id = [](int v) {
+    asm volatile("" : "+v"(v));
+    return v;
+  };
+  auto column_weight = [&](int a, float fx, float fy) {
+    return ((a >> 1) ? fx : 1.0f - fx) * ((a & 1) ? fy : 1.0f - fy);
+  };
+  const unsigned nxy = (unsigned)(P.nx * P.ny);
+  const int nodex = P.cx[cxi].n0, nodey = P.cy[cyi].n0;
+  const unsigned plane = (unsigned)(P.mx * P.my);
+  const unsigned nb = (unsigned)P.nbar, nxu = (unsigned)P.nx;
+
+  // the group's node block, as in diag_tile_kernel
+  const int lxa = x0 == 0 ? 1 : 0, lya = y0 == 0 ? 1 : 0;
+  const int lxb = min(BX - 1, P.mx - x0), lyb = min(BY - 1, P.my - y0);
+  const int nox = P.cx[x0 - 1 + lxa].n0, noy = P.cy[y0 - 1 + lya].n0;
+  const int nxl = P.cx[x0 - 1 + lxb].n0 + 2 - nox, nyl = P.cy[y0 - 1 + lyb].n0 + 2 - noy;
+  const int noz = P.cz[max(zb - 1, 0)].n0;
+  const int nzend = P.cz[min(ze, P.mz - 1)].n0 + 2;   // one past the block's last node plane
+
+  // weights of the cell's node columns n0, n0 + 1 of entry x at x - 1 and x + 1: 0
+  // outside the image and for nodes beyond the neighbour's own cell
+  auto neighbour_weights = [](const Conv1* c, int m, int x) {
+    const Conv1 a = c[x], l = c[max(x - 1, 0)], r = c[min(x + 1, m - 1)];
+    float4 w = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (x > 0) {
+      w.x = conv_weight(l, a.n0);
+      w.y = conv_weight(l, a.n0 + 1);
+    }
+    if (x < m - 1) {
+      w.z = conv_weight(r, a.n0);
+      w.w = conv_weight(r, a.n0 + 1);
+    }
+    return w;
+  };
+  for (int j = tid; j < ze - zb + 4; j += NT) {
+    const int q = min(max(zb - 2 + j, 0), P.mz - 1);
+    S.sCz[j] = P.cz[q];
+    S.sSz[j] = P.sz[q];
+    if constexpr (!SSD) S.sZw[j] = neighbour_weights(P.cz, P.mz, q);
+  }
+  auto axis_table = [&](const Conv1* c, const Samp1* sp, int m, int pitch, int i, Conv1& oc, typename Sm::Axis& o) {
+    const int x = min(max(i, 0), m - 1);
+    oc = c[x];
+    o.s = sp[x];
+    o.f = oc.f;
+    o.r = (unsigned)(x * pitch) << 2;
+    if constexpr (!SSD) {
+      o.w = neighbour_weights(c, m, x);
+      if constexpr (SCALED) {
+        o.w.x /= 1.0f - oc.f;
+        o.w.y /= oc.f;
+        o.w.z /= 1.0f - oc.f;
+        o.w.w /= oc.f;
+      }
+    }
+  };
+  if (tid < BX) axis_table(P.cx, P.sx, P.mx, 1, x0 - 1 + tid, S.sCx[tid], S.sAx[tid]);
+  if (tid >= 64 && tid - 64 < BY) axis_table(P.cy, P.sy, P.my, P.mx, y0 - 1 + tid - 64, S.sCy[tid - 64], S.sAy[tid - 64]);
+  // the neighbour beyond the cell's edge, if there is one
+  const bool ex_right = P.cx[min(cxi + 1, P.mx - 1)].n0 != nodex, ey_up = P.cy[min(cyi + 1, P.my - 1)].n0 != nodey;
+  if constexpr (!SSD) S.sCarry[0][tid] = S.sCarry[1][tid] = S.sCarry[2][tid] = 0.f;
+  if constexpr (XP > 0) {   // the pads of the plane exchange are never written by the march
+    for (int w = tid; w < 2 * 2 * XP; w += NT) {
+      const int r = w % (2 * XP), sl = w / (2 * XP);
+      const int q = r < XP ? r : NT + r;
+      S.sTw[sl][q] = 0.f;
+      S.sR[sl][q] = 0.f;
+      S.sG[sl][0][q] = S.sG[sl][1][q] = S.sG[sl][2][q] = 0.f;
+    }
+  }
+  __syncthreads();
+  if (tid < nxl) S.sNx[tid] = node_columns(S.sCx, BX, x0 - 1, P.mx, nox + tid);
+  if (tid >= 64 && tid - 64 < nyl) S.sNy[tid - 64] = node_columns(S.sCy, BY, y0 - 1, P.my, noy + tid - 64);
+
+  const int slot = tile_x + P.tiles_x * (tile_y + P.tiles_y * chunk);
+  float* const part = P.part + (size_t)slot * 3 * P.nzt * P.nyt * P.nxt;
+  const size_t dstride = (size_t)P.nzt * P.nyt * P.nxt;
+
+  // sums of the own column for node planes KL (lo) and KL + 1 (hi): the four node
+  // columns 2 i + j of the cell, the x and the y neighbour's squares; SSD: of g_d^2
+  constexpr int NA = SSD ? 1 : 4, NE = SSD ? 1 : 3;
+  float lo[3][NA], hi[3][NA], exl[NE], exh[NE], eyl[NE], eyh[NE];
+#pragma unroll
+  for (int d = 0; d < 3; ++d)
+#pragma unroll
+    for (int a = 0; a < NA; ++a) lo[d][a] = hi[d][a] = 0.f;
+#pragma unroll
+  for (int d = 0; d < NE; ++d) exl[d] = exh[d] = eyl[d] = eyh[d] = 0.f;
+  int KL = noz;
+
+  // Writes node plane KL and moves on to the next one.
+  auto flush = [&]() {
+    // (opaque here, so that none of its addresses is kept in registers over the march)
+    const int ft = opaque_id(tid);
+    const int fx = ft % BX, fy = ft / BX, o = (fy - 1) * BP + fx - 1;
+    const bool own = fx >= 1 && fx < BX - 1 && fy >= 1 && fy < BY - 1;
+    const float wx1 = S.sAx[fx].f, wy1 = S.sAy[fy].f;
+    if (own) {
+     if constexpr (SSD) {
+#pragma unroll
+      for (int d = 0; d < 3; ++d) S.sB[d][o] = lo[d][0];
+     } else {
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+          const float W = SCALED ? column_weight(a, wx1, wy1) : 1.0f;
+          S.sB[4 * d + a][o] = W * W * lo[d][a];
+        }
+        S.sB[12 + d][o] = exl[d];
+        S.sB[15 + d][o] = eyl[d];
+      }
+     }
+    }
+    __syncthreads();
+    // over the columns of each node, per own row inside the image
+    const int rows = min(TY, P.my - y0);
+    for (int w = ft; w < 3 * rows * nxl; w += NT) {
+      const int a = w % nxl, r = w / nxl, d = r % 3, l = r / 3;   // own row l: local row l + 1
+      const NodeCols nc = S.sNx[a];
+      if constexpr (SSD) {
+        float s = 0.f;
+        for (int t = nc.lo1; t < nc.hi1; ++t) {
+          const float f = S.sCx[t].f;
+          s = fmaf(f * f, S.sB[d][l * BP + t - 1], s);
+        }
+        for (int t = nc.lo0; t < nc.hi0; ++t) {
+          const float f = 1.0f - S.sCx[t].f;
+          s = fmaf(f * f, S.sB[d][l * BP + t - 1], s);
+        }
+        S.sC[d][l][a] = s;
+      } else {
+        float s0 = 0.f, s1 = 0.f, y = 0.f;
+        for (int t = nc.lo1; t < nc.hi1; ++t) {
+          const float f = S.sCx[t].f;
+          s0 += S.sB[4 * d + 2][l * BP + t - 1];
+          s1 += S.sB[4 * d + 3][l * BP + t - 1];
+          y = fmaf(f * f, S.sB[15 + d][l * BP + t - 1], y);
+        }
+        for (int t = nc.lo0; t < nc.hi0; ++t) {
+          const float f = 1.0f - S.sCx[t].f;
+          s0 += S.sB[4 * d][l * BP + t - 1];
+          s1 += S.sB[4 * d + 1][l * BP + t - 1];
+          y = fmaf(f * f, S.sB[15 + d][l * BP + t - 1], y);
+        }
+        float x = 0.f;
+        if (nc.e1 >= 0) x = nc.w1 * nc.w1 * S.sB[12 + d][l * BP + nc.e1 - 1];
+        if (nc.e2 >= 0) x = fmaf(nc.w2 * nc.w2, S.sB[12 + d][l * BP + nc.e2 - 1], x);
+        const float fv = S.sCy[l + 1].f;
+        S.sC[3 * d][l][a] = fmaf((1.0f - fv) * (1.0f - fv), x, s0);
+        S.sC[3 * d + 1][l][a] = fmaf(fv * fv, x, s1);
+        S.sC[3 * d + 2][l][a] = y;
+      }
+    }
+    __syncthreads();
+    // over the rows of each node
+    for (int w = ft; w < 3 * nyl * nxl; w += NT) {
+      const int a = w % nxl, r = w / nxl, b = r % nyl, d = r / nyl;
+      const NodeCols nc = S.sNy[b];
+      float s = 0.f;
+      if constexpr (SSD) {
+        for (int t = nc.lo1; t < nc.hi1; ++t) {
+          const float f = S.sCy[t].f;
+          s = fmaf(f * f, S.sC[d][t - 1][a], s);
+        }
+        for (int t = nc.lo0; t < nc.hi0; ++t) {
+          const float f = 1.0f - S.sCy[t].f;
+          s = fmaf(f * f, S.sC[d][t - 1][a], s);
+        }
+      } else {
+        for (int t = nc.lo1; t < nc.hi1; ++t) s += S.sC[3 * d + 1][t - 1][a];
+        for (int t = nc.lo0; t < nc.hi0; ++t) s += S.sC[3 * d][t - 1][a];
+        if (nc.e1 >= 0) s = fmaf(nc.w1 * nc.w1, S.sC[3 * d + 2][nc.e1 - 1][a], s);
+        if (nc.e2 >= 0) s = fmaf(nc.w2 * nc.w2, S.sC[3 * d + 2][nc.e2 - 1][a], s);
+      }
+      part[(size_t)d * dstride + ((size_t)(KL - noz) * P.nyt + b) * P.nxt + a] = s;
+    }
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      const float carry = SSD ? 0.f : S.sCarry[SSD ? 0 : d][SSD ? 0 : ft];
+#pragma unroll
+      for (int a = 0; a < NA; ++a) {
+        lo[d][a] = hi[d][a];
+        if constexpr (SSD) {
+          hi[d][a] = 0.f;
+        } else {
+          const float W = SCALED ? 1.0f : column_weight(a, wx1, wy1);
+          hi[d][a] = W * W * carry;
+        }
+      }
+      if constexpr (!SSD) {
+        exl[d] = exh[d];
+        eyl[d] = eyh[d];
+        exh[d] = eyh[d] = 0.f;
+        S.sCarry[d][ft] = 0.f;
+      }
+    }
+    ++KL;
+  };
+
+  // Register windows of the own column; slot (t - tfirst) mod 3.
+  float Tw[3] = {0.f, 0.f, 0.f}, Rv[3] = {0.f, 0.f, 0.f};
+  float g[3][3] = {{0.f, 0.f, 0.f}, {0.f, 0.f, 0.f}, {0.f, 0.f, 0.f}};
+
+  int Kp = -0x7fffffff;
+  float ulo[3] = {0.f, 0.f, 0.f}, udz[3] = {0.f, 0.f, 0.f};
+  const __amdgpu_buffer_rsrc_t rsT = raw_buffer(P.Tp, P.Tbytes), rsR = raw_buffer(P.R, P.Rbytes);
+  const CornerOffsets co{4u * (unsigned)P.PX, 4u * (unsigned)P.PXY, 4u * (unsigned)(P.PX + P.PXY)};
+  auto xy_interp = [&](int k, float (&o)[3]) {
+    const int lt = opaque_id(tid);
+    const Conv1 ex = S.sCx[lt % BX], ey = S.sCy[lt / BX];
+    const unsigned i00 = (unsigned)k * nxy + (unsigned)(ey.n0 * P.nx + ex.n0);
+    const float wx1 = ex.f, wy1 = ey.f, wx0 = 1.0f - wx1, wy0 = 1.0f - wy1;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      const unsigned b = (unsigned)d * nb + i00;
+      const float l = fmaf(wx1, ld32(u, b + 1), wx0 * ld32(u, b));
+      const float h = fmaf(wx1, ld32(u, b + nxu + 1), wx0 * ld32(u, b + nxu));
+      o[d] = fmaf(wy1, h, wy0 * l);
+    }
+  };
+
+  // stage-A inputs of the next plane, loaded one step ahead
+  float nx_t[8];
+  float nx_fx = 0.f, nx_fy = 0.f, nx_fz = 0.f, nx_R = 0.f;
+  auto issue = [&](int tt) {
+    const int tc = min(max(tt, 0), P.mz - 1);
+    const int jz = tt - zb + 2;
+    const Conv1 cvz = uniform_conv(S.sCz[jz]);
+    if (cvz.n0 != Kp) {   // both node planes are interpolated again (cached reads; fewer live registers)
+      float uhi[3];
+      xy_interp(cvz.n0, ulo);
+      xy_interp(cvz.n0 + 1, uhi);
+#pragma unroll
+      for (int d = 0; d < 3; ++d) udz[d] = uhi[d] - ulo[d];
+      Kp = cvz.n0;
+    }
+    const float fz = cvz.f;
+    const int lt = opaque_id(tid);
+    const auto &ax = S.sAx[lt % BX], &ay = S.sAy[lt / BX];
+    const int kx = template_cell(ax.s, fmaf(fz, udz[0], ulo[0]), P.ihTx, nx_fx);
+    const int ky = template_cell(ay.s, fmaf(fz, udz[1], ulo[1]), P.ihTy, nx_fy);
+    const int kz = template_cell(S.sSz[jz], fmaf(fz, udz[2], ulo[2]), P.ihTz, nx_fz);
+    template_corners_buf(P, rsT, co, kx, ky, kz, nx_t);
+    if constexpr (!SSD) nx_R = buf_ld(rsR, ax.r + ay.r, (unsigned)tc * plane * 4u);
+  };
+
+  const int tfirst = zb - 1, tlast = ze;
+
+  auto step = [&](auto Kc, int t) {
+    constexpr int K = decltype(Kc)::value;   // slot of plane t
+    constexpr int K1 = (K + 2) % 3;          // slot of plane t-1
+    constexpr int K2 = (K + 1) % 3;          // slot of plane t-2
+
+    // ---------------- stage A: plane t ----------------
+    {
+      const Tri s = trilinear(P, nx_t, nx_fx, nx_fy, nx_fz);
+      Tw[K] = s.v;
+      g[K][0] = s.gx;
+      g[K][1] = s.gy;
+      g[K][2] = s.gz;
+      Rv[K] = nx_R;
+      if constexpr (!SSD) {
+        const int sl = t & 1;
+        S.sTw[sl][XP + tid] = Tw[K];
+        S.sR[sl][XP + tid] = Rv[K];
+        S.sG[sl][0][XP + tid] = s.gx;
+        S.sG[sl][1][XP + tid] = s.gy;
+        S.sG[sl][2][XP + tid] = s.gz;
+      }
+    }
+    if (t < tlast) issue(t + 1);
+
+    // ---------------- row plane c = t-1 ----------------
+    const int c = t - 1;
+    if (c >= zb) {   // uniform: the first two steps sample planes zb-1 and zb only
+      const Conv1 cz0 = uniform_conv(S.sCz[c - zb + 2]);
+      const float wz[2] = {uniform_f(1.0f - cz0.f), cz0.f};
+      if constexpr (SSD) {
+        if (cz0.n0 != KL) flush();
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+          const float a = wz[0] * g[K1][d], b = wz[1] * g[K1][d];
+          lo[d][0] = fmaf(a, a, lo[d][0]);
+          hi[d][0] = fmaf(b, b, hi[d][0]);
+        }
+      } else {
+        const int s1 = c & 1;
+        const int q = XP + tid;
+        const float Tc = Tw[K1], Rc = Rv[K1];
+        const float dTxm = S.sTw[s1][q - 1] - Tc, dTxp = S.sTw[s1][q + 1] - Tc;
+        const float dTym = S.sTw[s1][q - BX] - Tc, dTyp = S.sTw[s1][q + BX] - Tc;
+        const float dTzm = Tw[K2] - Tc, dTzp = Tw[K] - Tc;
+        const float dRxm = S.sR[s1][q - 1] - Rc, dRxp = S.sR[s1][q + 1] - Rc;
+        const float dRym = S.sR[s1][q - BX] - Rc, dRyp = S.sR[s1][q + BX] - Rc;
+        const float dRzm = Rv[K2] - Rc, dRzp = Rv[K] - Rc;
+        const float sTT = fmaf(fmaf(dTxm, dTxm, dTxp * dTxp), P.ih2x,
+                               fmaf(fmaf(dTym, dTym, dTyp * dTyp), P.ih2y, fmaf(dTzm, dTzm, dTzp * dTzp) * P.ih2z));
+        const float sRR = fmaf(fmaf(dRxm, dRxm, dRxp * dRxp), P.ih2x,
+                               fmaf(fmaf(dRym, dRym, dRyp * dRyp), P.ih2y, fmaf(dRzm, dRzm, dRzp * dRzp) * P.ih2z));
+        const float sTR = fmaf(fmaf(dTxm, dRxm, dTxp * dRxp), P.ih2x,
+                               fmaf(fmaf(dTym, dRym, dTyp * dRyp), P.ih2y, fmaf(dTzm, dRzm, dTzp * dRzp) * P.ih2z));
+        const float nT2 = fmaf(0.5f, sTT, P.tau2);
+        const float nR2 = fmaf(0.5f, sRR, P.rho2);
+        const float r1 = fmaf(0.5f, sTR, P.taurho);
+        const float rnT = rsq_norm(nT2), rnR = rsq_norm(nR2);
+        const float c1 = rnT * rnR;
+        const float c2 = r1 * rnT * rnT;
+        const float kx = P.hhx * c1, ky = P.hhy * c1, kz = P.hhz * c1;
+        const float rxm = kx * fmaf(-c2, dTxm, dRxm), rxp = kx * fmaf(-c2, dTxp, dRxp);
+        const float rym = ky * fmaf(-c2, dTym, dRym), ryp = ky * fmaf(-c2, dTyp, dRyp);
+        const float rzm = kz * fmaf(-c2, dTzm, dRzm), rzp = kz * fmaf(-c2, dTzp, dRzp);
+        const float r0 = -(((rxm + rxp) + (rym + ryp)) + (rzm + rzp));
+        const float pzm[3] = {rzm * g[K2][0], rzm * g[K2][1], rzm * g[K2][2]};
+        if (cz0.n0 != KL) {
+          // node plane KL gets the -z products of this plane alone (from a plane of
+          // the cell below, which is inside the image) and is complete then
+          const int lt = opaque_id(tid);
+          const float wze = 1.0f - S.sCz[c - zb + 1].f, wx1 = S.sAx[lt % BX].f, wy1 = S.sAy[lt / BX].f;
+#pragma unroll
+          for (int d = 0; d < 3; ++d) {
+            const float e = wze * pzm[d];
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+              const float z = SCALED ? e : column_weight(a, wx1, wy1) * e;
+              lo[d][a] = fmaf(z, z, lo[d][a]);
+            }
+          }
+          flush();
+        }
+        const float4 zw = S.sZw[c - zb + 2];
+        const float wz2[2] = {uniform_f(wz[0] * wz[0]), uniform_f(wz[1] * wz[1])};
+        const float zm[2] = {uniform_f(zw.x), uniform_f(zw.y)}, zp[2] = {uniform_f(zw.z), uniform_f(zw.w)};
+        const int lt = opaque_id(tid);
+        const float4 wx = S.sAx[lt % BX].w, wy = S.sAy[lt / BX].w;
+        const float fx = S.sAx[lt % BX].f, fy = S.sAy[lt / BX].f;
+        const float w0[2] = {1.0f - fx, fx}, v0[2] = {1.0f - fy, fy};
+        const float wm[2] = {wx.x, wx.y}, wp[2] = {wx.z, wx.w}, vm[2] = {wy.x, wy.y}, vp[2] = {wy.z, wy.w};
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+          __builtin_amdgcn_sched_barrier(0);   // (registers: one component at a time)
+          const float p0 = r0 * g[K1][d];
+          const float pxm = rxm * S.sG[s1][d][q - 1], pxp = rxp * S.sG[s1][d][q + 1];
+          const float pym = rym * S.sG[s1][d][q - BX], pyp = ryp * S.sG[s1][d][q + BX];
+          const float pzp = rzp * g[K][d];
+          const float Z0 = fmaf(zp[0], pzp, zm[0] * pzm[d]), Z1 = fmaf(zp[1], pzp, zm[1] * pzm[d]);
+          float U[2], V[2];
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            U[i] = fmaf(wp[i], pxp, fmaf(wm[i], pxm, SCALED ? p0 : w0[i] * p0));
+            V[i] = fmaf(vp[i], pyp, vm[i] * pym);
+          }
+#pragma unroll
+          for (int a = 0; a < 4; ++a) {
+            const int i = a >> 1, j = a & 1;
+            const float W = w0[i] * v0[j];
+            const float pxy = SCALED ? U[i] + V[j] : fmaf(v0[j], U[i], w0[i] * V[j]);
+            const float z0 = fmaf(wz[0], pxy, SCALED ? Z0 : W * Z0), z1 = fmaf(wz[1], pxy, SCALED ? Z1 : W * Z1);
+            lo[d][a] = fmaf(z0, z0, lo[d][a]);
+            hi[d][a] = fmaf(z1, z1, hi[d][a]);
+          }
+          float ex = ex_right ? pxp : pxm, ey = ey_up ? pyp : pym;
+          ex *= ex;
+          ey *= ey;
+          exl[d] = fmaf(wz2[0], ex, exl[d]);
+          exh[d] = fmaf(wz2[1], ex, exh[d]);
+          eyl[d] = fmaf(wz2[0], ey, eyl[d]);
+          eyh[d] = fmaf(wz2[1], ey, eyh[d]);
+        }
+        const Conv1 czp = S.sCz[c - zb + 3];
+        if (__builtin_amdgcn_readfirstlane(czp.n0) != cz0.n0) {   // the +z products reach node plane KL + 2
+#pragma unroll
+          for (int d = 0; d < 3; ++d) {
+            const float e = czp.f * (rzp * g[K][d]);
+            S.sCarry[d][lt] = e * e;
+          }
+        }
+      }
+    }
+    // the exchange slots of plane t are complete; those of t-1 are free
+    if constexpr (!SSD) __syncthreads();
+  };
+
+  issue(tfirst);
+  for (int t = tfirst; t <= tlast; t += 3) {
+    step(std::integral_constant<int, 0>{}, t);
+    if (t + 1 <= tlast) step(std::integral_constant<int, 1>{}, t + 1);
+    if (t + 2 <= tlast) step(std::integral_constant<int, 2>{}, t + 2);
+  }
+  while (KL < nzend) flush();
+}
+
 // The same for a two-dimensional problem (d = 2): a group of kPlaneNT threads
 // covers kPlaneNT pixel columns (own inner columns and a one-column ring) and
 // marches through a chunk of pixel rows; a row of dr has five entries (0, -x,
@@ -791,10 +1300,17 @@ hipError_t launch_diag_tile(const DiagTileParams& d, const float* u, float* diag
     hipLaunchKernelGGL(diag_node_kernel, dim3((d.t.nbar + 255) / 256, 2), dim3(256), 0, st, d, diag);
     return hipGetLastError();
   }
-  if (d.t.ssd)
-    hipLaunchKernelGGL((diag_tile_kernel<true>), dim3(grid), dim3(kDiagBX * kDiagBY), 0, st, d, u);
+  const dim3 blk(kDiagBX * kDiagBY);
+  if (d.march && d.t.ssd)
+    hipLaunchKernelGGL((diag_march_kernel<true, false>), dim3(grid), blk, 0, st, d, u);
+  else if (d.march == 2)
+    hipLaunchKernelGGL((diag_march_kernel<false, true>), dim3(grid), blk, 0, st, d, u);
+  else if (d.march)
+    hipLaunchKernelGGL((diag_march_kernel<false, false>), dim3(grid), blk, 0, st, d, u);
+  else if (d.t.ssd)
+    hipLaunchKernelGGL((diag_tile_kernel<true>), dim3(grid), blk, 0, st, d, u);
   else
-    hipLaunchKernelGGL((diag_tile_kernel<false>), dim3(grid), dim3(kDiagBX * kDiagBY), 0, st, d, u);
+    hipLaunchKernelGGL((diag_tile_kernel<false>), dim3(grid), blk, 0, st, d, u);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(diag_node_kernel, dim3((d.t.nbar + 255) / 256, 3), dim3(256), 0, st, d, diag);

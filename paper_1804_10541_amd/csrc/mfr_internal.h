@@ -144,6 +144,9 @@ struct DiagParams {
 // nyt, nzt and part describe it: kDiagBX x kDiagBY groups), and the node pass
 // that sums the partial diagonal blocks of the tiles overlapping each node.
 constexpr int kDiagBX = 32, kDiagBY = 16;
+// most nodes of a group along x and y where every cell has at least two voxels
+constexpr int kMarchNX = kDiagBX / 2 + 2, kMarchNY = kDiagBY / 2 + 2;
+constexpr int kMarchChunk = 124;   // most planes of a chunk there
 struct DiagTileParams {
   TileParams t;
   const Range1* rx;   // per node index: voxel rows whose dr row touches the node's support
@@ -157,6 +160,8 @@ struct DiagTileParams {
   float s_ngf;        // 2 hbar (hbar for SSD)
   float s_curv;       // regulariser scale
   float ihy2x, ihy2y, ihy2z;
+  int march;          // at least two voxels per cell in x and y: the sums stay with the columns (2: divided by
+                      // the weights, which are all clear of 0)
   int plane;          // two-dimensional problem: x tiles and row chunks (as y tiles) of kPlaneNT columns
 };
 
