@@ -101,7 +101,7 @@ def c4_specs():
 
 def batch_leg(dev, tune):
     """Multilevel registration of the ten uneven pairs: the batched path (one
-    persistent launch per phase for all pairs, CG iterations replayed from
+    launch per phase for all pairs, CG iterations replayed from
     captured HIP graphs) against per-pair runs of the single-pair path, and a
     check that both return the same displacements bit for bit."""
     import torch

@@ -386,9 +386,8 @@ mfr_status mfr_lbfgs(mfr_ctx* ctx, float* u, const mfr_lbfgs_opts* opts, void* w
 /* ---- Batched registration of independent pairs ------------------------------
  * Up to MFR_MAX_BATCH image pairs of different sizes advance together: every
  * phase (voxel-tile kernels, node passes, sums, CG vector updates) is one
- * launch for all pairs; the voxel-tile kernels are persistent (work-groups take
- * tiles of any pair from a shared device counter).  The CG iteration is steered
- * on the device (per-pair convergence flags), so a block of iterations is
+ * launch for all pairs (the voxel-tile kernels over the joined tile list of all
+ * pairs).  The CG iteration is steered on the device (per-pair convergence flags), so a block of iterations is
  * captured once into a HIP graph and replayed.  Results equal running each pair
  * alone through mfr_register_multilevel, bit for bit.  This is an extension of
  * the paper's single-pair method (Sec. 2.3) for throughput; it is not in the
@@ -423,7 +422,7 @@ void mfr_batch_destroy(mfr_batch* b);
 mfr_status mfr_batch_set_images(mfr_batch* b, const float* const* R, const float* const* T);
 
 /* q_i = (H_i + alpha nabla^2 S_i) p_i at u_i on the finest grids, every pair in
- * one persistent launch (host arrays of n device pointers).  Asynchronous. */
+ * one launch (host arrays of n device pointers).  Asynchronous. */
 mfr_status mfr_batch_hess_vec(mfr_batch* b, const float* const* u, const float* const* p, float* const* q);
 
 /* Coarse-to-fine Gauss-Newton registration of every pair (options as in

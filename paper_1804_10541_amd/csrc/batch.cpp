@@ -23,13 +23,11 @@ struct mfr_batch {
   std::vector<size_t> base;             // per pair: offset of its region
   std::vector<size_t> ctx_bytes;        // per pair: context workspace (largest level)
   std::vector<size_t> off_ptab;         // per pair: prolongation tables
-  size_t off_ctrl = 0;                  // counter, active flags, CG state, scalars
-  int* counter = nullptr;
+  size_t off_ctrl = 0;                  // active flags, CG state, scalars
   int* active = nullptr;                // per pair: CG active flag (written by the CG kernels)
   int* mask = nullptr;                  // per pair: host-set mask for Gauss-Newton phases
   int* state = nullptr;                 // per pair: ST_COUNT ints
   double* sc = nullptr;                 // per pair: SC_COUNT doubles
-  int groups = 0;                       // persistent work-groups of a voxel-tile launch (0: resident capacity)
   int cur = -1;                         // level the contexts are built for
   mfr_ctx* ctx[kMaxBatch] = {};
   bool images = false;
@@ -77,7 +75,7 @@ mfr_status batch_layout(int n, const mfr_grid* grids, int levels, mfr_batch* b, 
     o = align_up(o + per);
   }
   b->off_ctrl = o;
-  o = align_up(o + sizeof(int) * (1 + 2 * kMaxBatch + ST_COUNT * kMaxBatch));
+  o = align_up(o + sizeof(int) * (2 * kMaxBatch + ST_COUNT * kMaxBatch));
   o = align_up(o + sizeof(double) * SC_COUNT * kMaxBatch);
   *total = o;
   return MFR_OK;
@@ -119,7 +117,7 @@ mfr_status read_back(mfr_batch* b, void* dst, const void* src, size_t bytes) {
   return MFR_OK;
 }
 
-// Fills the persistent work list of a voxel-tile launch.
+// Fills the work list of a voxel-tile launch.
 BatchJobs tile_jobs(mfr_batch* b, const float* const* u, const float* const* p, const int* active) {
   BatchJobs J{};
   J.n = b->n;
@@ -131,7 +129,6 @@ BatchJobs tile_jobs(mfr_batch* b, const float* const* u, const float* const* p, 
     J.prefix[k + 1] = J.prefix[k] + b->ctx[k]->tiling.grid();
   }
   J.total = J.prefix[b->n];
-  J.counter = b->counter;
   J.active = active;
   return J;
 }
@@ -153,8 +150,7 @@ NodeJobs node_jobs(mfr_batch* b, float s_ngf_scale, const float* const* f, float
 }
 
 mfr_status launch_tiles(mfr_batch* b, int mode, const BatchJobs& J) {
-  HIP_TRY(launch_zero_ints(b->counter, 1, b->st));   // a kernel, not a memset: capturable
-  HIP_TRY(launch_tile_batch(b->ctx[0]->tiling.shape, mode, J, b->groups, b->st));
+  HIP_TRY(launch_tile_batch(b->ctx[0]->tiling.shape, mode, J, b->st));
   return MFR_OK;
 }
 
@@ -366,12 +362,10 @@ mfr_status mfr_batch_create(int32_t n, const mfr_grid* grids, int32_t levels, vo
   b->st = reinterpret_cast<hipStream_t>(hip_stream);
   b->ws = reinterpret_cast<char*>(workspace);
   int* ip = reinterpret_cast<int*>(b->ws + b->off_ctrl);
-  b->counter = ip;
-  b->active = ip + 1;
-  b->mask = ip + 1 + kMaxBatch;
-  b->state = ip + 1 + 2 * kMaxBatch;
-  b->sc = reinterpret_cast<double*>(b->ws + align_up(b->off_ctrl + sizeof(int) * (1 + 2 * kMaxBatch + ST_COUNT * kMaxBatch)));
-  b->groups = 0;   // persistent launches: as many work-groups as are resident at once
+  b->active = ip;
+  b->mask = ip + kMaxBatch;
+  b->state = ip + 2 * kMaxBatch;
+  b->sc = reinterpret_cast<double*>(b->ws + align_up(b->off_ctrl + sizeof(int) * (2 * kMaxBatch + ST_COUNT * kMaxBatch)));
   *out = b;
   return MFR_OK;
 }

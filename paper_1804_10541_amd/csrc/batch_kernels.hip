@@ -66,15 +66,6 @@ hipError_t launch_sum_batch(const SumJobs& j, hipStream_t st) {
   return hipGetLastError();
 }
 
-__global__ void zero_ints_kernel(int* p, int n) {
-  for (int i = threadIdx.x; i < n; i += blockDim.x) p[i] = 0;
-}
-
-hipError_t launch_zero_ints(int* p, int n, hipStream_t st) {
-  hipLaunchKernelGGL(zero_ints_kernel, dim3(1), dim3(64), 0, st, p, n);
-  return hipGetLastError();
-}
-
 // ---- batched vector kernels ------------------------------------------------------
 // y_j = x_j + eta_j s_j for active problems
 __global__ __launch_bounds__(kVecBlock) void axpy_batch_kernel(const AxpyJobs J) {

@@ -198,16 +198,14 @@ struct BatchJob {
   const float* p;
 };
 
-// Work list of a persistent batched launch (passed by value, so the table
-// sits in kernel-argument memory): problem j owns tiles [prefix[j],
-// prefix[j+1]); counter is a device int the caller zeroes before the launch;
+// Work list of a batched launch (passed by value, so the table sits in
+// kernel-argument memory): problem j owns tiles [prefix[j], prefix[j+1]);
 // active (may be null) masks problems out.
 constexpr int kMaxBatch = 12;
 struct BatchJobs {
   BatchJob jobs[kMaxBatch];
   int prefix[kMaxBatch + 1];
   int n, total;
-  int* counter;
   const int* active;
 };
 
@@ -277,8 +275,7 @@ struct VecJobs {
 // ---- launch wrappers (return hipError_t of the launch) ----------------------
 hipError_t launch_tile(const TileShape& s, int mode, const TileParams& p, const float* u,
                        const float* pv, int grid, hipStream_t st);
-// groups <= 0: as many work-groups as fit on the device at once.
-hipError_t launch_tile_batch(const TileShape& s, int mode, const BatchJobs& j, int groups, hipStream_t st);
+hipError_t launch_tile_batch(const TileShape& s, int mode, const BatchJobs& j, hipStream_t st);
 hipError_t launch_node_pass(int mode, const NodeParams& q, const float* f, float* out, int blocks,
                             hipStream_t st);
 hipError_t launch_sum(const double* parts, int n, double* out, hipStream_t st);
@@ -349,7 +346,6 @@ hipError_t launch_prolong(const float* coarse, int cnx, int cny, int cnz, float*
 // batched path
 hipError_t launch_node_pass_batch(int mode, const NodeJobs& j, hipStream_t st);
 hipError_t launch_sum_batch(const SumJobs& j, hipStream_t st);
-hipError_t launch_zero_ints(int* p, int n, hipStream_t st);
 hipError_t launch_axpy_batch(const AxpyJobs& j, hipStream_t st);
 hipError_t launch_dot_batch(const VecJobs& j, hipStream_t st);
 hipError_t launch_pcg_init_batch(const VecJobs& j, hipStream_t st);
