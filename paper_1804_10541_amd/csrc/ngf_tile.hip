@@ -78,6 +78,9 @@ struct TileSmem {
   float sWx[NEED_C ? XT : 1][NEED_C ? BX / 4 : 1][NEED_C ? 64 : 1];
   float sWy[NEED_C ? YT : 1][NEED_C ? 4 * RT : 1][NEED_C ? 64 : 1];
   Conv1 sCx[BX], sCy[BY];
+  // u and p of the own column at the upper one of the two node planes in use (own
+  // slot only): read when the march passes to the next node plane, not kept in registers
+  float sHi[HV ? 6 : 3][NT];
   // z conversion and template-coordinate entries of planes zb-2 .. ze+1 (clamped
   // into the image): read at a uniform index every plane, from LDS rather than
   // through a vector load whose latency would sit on every step's address path
@@ -135,11 +138,13 @@ __device__ __forceinline__ void tile_body(const TileParams& P, const int bid, co
 
   // own column, clamped into the image
   const int cxi = min(max(gx, 0), P.mx - 1), cyi = min(max(gy, 0), P.my - 1);
-  const Conv1 cvx = P.cx[cxi], cvy = P.cy[cyi];
   const Samp1 spx = P.sx[cxi], spy = P.sy[cyi];
-  const float wx0 = 1.0f - cvx.f, wx1 = cvx.f, wy0 = 1.0f - cvy.f, wy1 = cvy.f;
+  // Template cells are counted from the padded template's first one (cell -2); its byte
+  // pitches, which a 24-bit multiply (full rate) takes where they fit.
+  const int bx2 = spx.base + 2, by2 = spy.base + 2;
+  const unsigned px4 = 4u * (unsigned)P.PX, pxy4 = 4u * (unsigned)P.PXY;
+  const bool mul24 = pxy4 < (1u << 24) && px4 < (1u << 24);
   const unsigned nxy = (unsigned)(P.nx * P.ny);
-  const unsigned nodexy = (unsigned)(cvy.n0 * P.nx + cvx.n0);
   const unsigned plane = (unsigned)(P.mx * P.my);
   const unsigned colxy = (unsigned)(cyi * P.mx + cxi);
   const unsigned nb = (unsigned)P.nbar, nxu = (unsigned)P.nx;
@@ -152,9 +157,13 @@ __device__ __forceinline__ void tile_body(const TileParams& P, const int bid, co
   for (int j = tid; j < ze - zb + 4; j += NT) {
     const int q = min(max(zb - 2 + j, 0), P.mz - 1);
     sCz[j] = P.cz[q];
-    sSz[j] = P.sz[q];
+    Samp1 e = P.sz[q];
+    e.base += 2;   // counted from the padded template's first plane
+    sSz[j] = e;
   }
-  if constexpr (!NEED_C) __syncthreads();   // (with NEED_C the barrier after sCx / sCy covers it)
+  if (tid < BX) sCx[tid] = P.cx[min(max(x0 - 1 + tid, 0), P.mx - 1)];
+  if (tid < BY) sCy[tid] = P.cy[min(max(y0 - 1 + tid, 0), P.my - 1)];
+  __syncthreads();
   constexpr int XP = TileSmem<BX, BY, MODE, SSD>::XP;
   if constexpr (XP > 0) {   // nor are the pads of the plane exchange
     for (int w = tid; w < 2 * 2 * XP; w += NT) {
@@ -174,9 +183,6 @@ __device__ __forceinline__ void tile_body(const TileParams& P, const int bid, co
   const int nxl = P.cx[x0 - 1 + lxb].n0 + 2 - nox;
   const int nyl = P.cy[y0 - 1 + lyb].n0 + 2 - noy;
   if constexpr (NEED_C) {
-    if (tid < BX) sCx[tid] = P.cx[min(max(x0 - 1 + tid, 0), P.mx - 1)];
-    if (tid < BY) sCy[tid] = P.cy[min(max(y0 - 1 + tid, 0), P.my - 1)];
-    __syncthreads();
     for (int w = tid; w < ((nxl + 15) / 16) * (BX / 4) * 64; w += NT) {
       const int c16 = w & 15, l = (w >> 4) % BX, nt = w / (16 * BX);   // lane (l & 3, c16) of step l / 4
       sWx[nt][l >> 2][w & 63] = conv_weight(sCx[l], nox + 16 * nt + c16);
@@ -308,6 +314,7 @@ __device__ __forceinline__ void tile_body(const TileParams& P, const int bid, co
 
   // Register windows of the own column; slot (t - tfirst) mod 3.
   float Tw[3] = {0.f, 0.f, 0.f}, Rv[3] = {0.f, 0.f, 0.f}, av[3] = {0.f, 0.f, 0.f};
+  float dzT[3] = {0.f, 0.f, 0.f}, dzR[3] = {0.f, 0.f, 0.f};   // differences to the plane before
   float g[3][3] = {{0.f, 0.f, 0.f}, {0.f, 0.f, 0.f}, {0.f, 0.f, 0.f}};
   float e0[3] = {0.f, 0.f, 0.f}, ezp[3] = {0.f, 0.f, 0.f};
   float acc_lo[3] = {0.f, 0.f, 0.f}, acc_hi[3] = {0.f, 0.f, 0.f};
@@ -317,15 +324,16 @@ __device__ __forceinline__ void tile_body(const TileParams& P, const int bid, co
   // xy-interpolated u and p at the two node planes bracketing the current plane,
   // and their differences (the z interpolation of every plane in between is one FMA)
   int Kp = -0x7fffffff;
-  float ulo[3] = {0.f, 0.f, 0.f}, uhi[3] = {0.f, 0.f, 0.f}, udz[3] = {0.f, 0.f, 0.f};
-  float plo[3] = {0.f, 0.f, 0.f}, phi[3] = {0.f, 0.f, 0.f}, pdz[3] = {0.f, 0.f, 0.f};
+  float ulo[3] = {0.f, 0.f, 0.f}, udz[3] = {0.f, 0.f, 0.f};
+  float plo[3] = {0.f, 0.f, 0.f}, pdz[3] = {0.f, 0.f, 0.f};
   // template and reference through buffer descriptors: the corner loads share one
   // vector offset, the reference load needs only the plane's scalar offset
   const __amdgpu_buffer_rsrc_t rsT = raw_buffer(P.Tp, P.Tbytes), rsR = raw_buffer(P.R, P.Rbytes);
   const CornerOffsets co{4u * (unsigned)P.PX, 4u * (unsigned)P.PXY, 4u * (unsigned)(P.PX + P.PXY)};
   const unsigned rcol = colxy << 2;
-  auto xy_interp = [&](const float* __restrict__ f, int k, float (&o)[3]) {
-    const unsigned i00 = (unsigned)k * nxy + nodexy;
+  auto xy_interp = [&](const float* __restrict__ f, int k, const Conv1 cvx, const Conv1 cvy, float (&o)[3]) {
+    const float wx0 = 1.0f - cvx.f, wx1 = cvx.f, wy0 = 1.0f - cvy.f, wy1 = cvy.f;
+    const unsigned i00 = (unsigned)k * nxy + (unsigned)(cvy.n0 * P.nx + cvx.n0);
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
       const unsigned b = (unsigned)d * nb + i00;
@@ -346,30 +354,61 @@ __device__ __forceinline__ void tile_body(const TileParams& P, const int bid, co
     cvz.n0 = __builtin_amdgcn_readfirstlane(cvz.n0);   // uniform: keeps the plane logic scalar
     cvz.f = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, cvz.f)));
     if (cvz.n0 != Kp) {
+      int ct = tid;   // (opaque, so that nothing of the column's weights is kept over the march)
+      asm volatile("" : "+v"(ct));
+      const Conv1 cvx = sCx[ct % BX], cvy = sCy[ct / BX];
       if (cvz.n0 == Kp + 1) {
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
-          ulo[d] = uhi[d];
-          if (HV) plo[d] = phi[d];
+          ulo[d] = S.sHi[d][ct];
+          if (HV) plo[d] = S.sHi[HV ? 3 + d : 0][ct];
         }
       } else {
-        xy_interp(u, cvz.n0, ulo);
-        if (HV) xy_interp(pv, cvz.n0, plo);
+        xy_interp(u, cvz.n0, cvx, cvy, ulo);
+        if (HV) xy_interp(pv, cvz.n0, cvx, cvy, plo);
       }
-      xy_interp(u, cvz.n0 + 1, uhi);
-      if (HV) xy_interp(pv, cvz.n0 + 1, phi);
+      float uhi[3], phi[3];
+      xy_interp(u, cvz.n0 + 1, cvx, cvy, uhi);
+      if (HV) xy_interp(pv, cvz.n0 + 1, cvx, cvy, phi);
 #pragma unroll
       for (int d = 0; d < 3; ++d) {
+        S.sHi[d][ct] = uhi[d];
         udz[d] = uhi[d] - ulo[d];
-        if (HV) pdz[d] = phi[d] - plo[d];
+        if (HV) {
+          S.sHi[HV ? 3 + d : 0][ct] = phi[d];
+          pdz[d] = phi[d] - plo[d];
+        }
       }
       Kp = cvz.n0;
     }
     const float fz = cvz.f;
-    const int kx = template_cell(spx, fmaf(fz, udz[0], ulo[0]), P.ihTx, nx_fx);
-    const int ky = template_cell(spy, fmaf(fz, udz[1], ulo[1]), P.ihTy, nx_fy);
-    const int kz = template_cell(sSz[jz], fmaf(fz, udz[2], ulo[2]), P.ihTz, nx_fz);
-    template_corners_buf(P, rsT, co, kx, ky, kz, nx_t);
+    const float qx = template_pos(spx.frac, fmaf(fz, udz[0], ulo[0]), P.ihTx, nx_fx);
+    const float qy = template_pos(spy.frac, fmaf(fz, udz[1], ulo[1]), P.ihTy, nx_fy);
+    const Samp1 spz = sSz[jz];
+    const float qz = template_pos(spz.frac, fmaf(fz, udz[2], ulo[2]), P.ihTz, nx_fz);
+    const unsigned kx = (unsigned)clamp_lo0(bx2 + floor_to_int(qx), P.mTx + 2);
+    const unsigned ky = (unsigned)clamp_lo0(by2 + floor_to_int(qy), P.mTy + 2);
+    const unsigned kz = (unsigned)clamp_lo0(spz.base + floor_to_int(qz), P.mTz + 2);
+    unsigned v;
+    if (mul24)
+      v = __umul24(kz, pxy4) + __umul24(ky, px4);
+    else {
+      asm volatile("");   // (a branch: the full multiplies stay out of the common path)
+      v = kz * pxy4 + ky * px4;
+    }
+    v += kx << 2;
+    {
+      const FPair a = buf_ld2(rsT, v, 0), b = buf_ld2(rsT, v, co.row), c = buf_ld2(rsT, v, co.plane),
+                  d = buf_ld2(rsT, v, co.both);
+      nx_t[0] = a.a;
+      nx_t[1] = a.b;
+      nx_t[2] = b.a;
+      nx_t[3] = b.b;
+      nx_t[4] = c.a;
+      nx_t[5] = c.b;
+      nx_t[6] = d.a;
+      nx_t[7] = d.b;
+    }
     nx_R = buf_ld(rsR, rcol, (unsigned)tc * plane * 4u);
     if (HV) {
 #pragma unroll
@@ -377,9 +416,11 @@ __device__ __forceinline__ void tile_body(const TileParams& P, const int bid, co
     }
   };
 
-  const int tfirst = zb - 2, tlast = ze + 1;
+  // Rows are formed at planes zb - 1 .. ze, of which the image's first chunk has no
+  // plane -1: two steps of stage A alone, then all three stages per step.
+  const int tfirst = max(zb - 2, -1), tlast = ze + 1;
 
-  auto step = [&](auto Kc, int t) {
+  auto step = [&](auto Kc, auto Lead, int t) {
     constexpr int K = decltype(Kc)::value;   // slot of plane t
     constexpr int K1 = (K + 2) % 3;          // slot of plane t-1
     constexpr int K2 = (K + 1) % 3;          // slot of plane t-2
@@ -392,6 +433,8 @@ __device__ __forceinline__ void tile_body(const TileParams& P, const int bid, co
       g[K][1] = s.gy;
       g[K][2] = s.gz;
       Rv[K] = nx_R;
+      dzT[K] = Tw[K] - Tw[K1];
+      dzR[K] = Rv[K] - Rv[K1];
       if (HV) av[K] = fmaf(s.gx, nx_pp[0], fmaf(s.gy, nx_pp[1], s.gz * nx_pp[2]));
       if constexpr (!SSD) {
         const int sl = t & 1;
@@ -405,82 +448,80 @@ __device__ __forceinline__ void tile_body(const TileParams& P, const int bid, co
     // previous step) and the slots written above were last read before the
     // barrier that ends the previous step.
 
+    if constexpr (decltype(Lead)::value) {
+      if constexpr (!SSD) __syncthreads();
+      return;
+    }
+
     // ---------------- stage B: plane zc = t-1 ----------------
     const int zc = t - 1;
     float ezm = 0.f;
-    e0[K1] = 0.f;
-    ezp[K1] = 0.f;
-    const bool zin = zc >= zb - 1 && zc <= ze && zc >= 0 && zc < P.mz;   // uniform
-    if (SSD && zin) {
-      if (inB) {
-        const float r = Tw[K1] - Rv[K1];
-        if (MODE != MODE_HV && zc >= zb && zc < ze) {
-          const double rd = r;
-          obj += 0.5 * rd * rd;
-        }
-        if constexpr (NEED_C) e0[K1] = HV ? av[K1] : r;
+    if constexpr (SSD) {
+      const float r = Tw[K1] - Rv[K1];
+      if (MODE != MODE_HV && inB && zc >= zb && zc < ze) {
+        const double rd = r;
+        obj += 0.5 * rd * rd;
       }
-    } else if (!SSD && zin) {
+      if constexpr (NEED_C) e0[K1] = inB ? (HV ? av[K1] : r) : 0.f;
+    } else {
       // Every lane evaluates the row (ring columns and columns outside the image
       // read finite neighbours: clamped samples or the zero pads), and a lane
-      // that does not own its row scales z by 0, which zeroes all its products:
-      // no divergent branch and no per-step clearing of the products.
+      // that does not own its row scales the products by 0: no divergent branch
+      // and no per-step clearing of the products.  The row plane behind the image's
+      // last one gets 1 / |grad T|^2 = 0 instead, which zeroes its products.
       const int s1 = zc & 1;
       const int q = XP + tid;
       const float Tc = Tw[K1], Rc = Rv[K1];
       const float dTxm = sTw[s1][q - 1] - Tc, dTxp = sTw[s1][q + 1] - Tc;
       const float dTym = sTw[s1][q - BX] - Tc, dTyp = sTw[s1][q + BX] - Tc;
-      const float dTzm = Tw[K2] - Tc, dTzp = Tw[K] - Tc;
+      const float dTzm = -dzT[K1], dTzp = dzT[K];
       const float dRxm = sR[s1][q - 1] - Rc, dRxp = sR[s1][q + 1] - Rc;
       const float dRym = sR[s1][q - BX] - Rc, dRyp = sR[s1][q + BX] - Rc;
-      const float dRzm = Rv[K2] - Rc, dRzp = Rv[K] - Rc;
-      const float sTT = fmaf(fmaf(dTxm, dTxm, dTxp * dTxp), P.ih2x,
-                             fmaf(fmaf(dTym, dTym, dTyp * dTyp), P.ih2y,
-                                  fmaf(dTzm, dTzm, dTzp * dTzp) * P.ih2z));
-      const float sRR = fmaf(fmaf(dRxm, dRxm, dRxp * dRxp), P.ih2x,
-                             fmaf(fmaf(dRym, dRym, dRyp * dRyp), P.ih2y,
-                                  fmaf(dRzm, dRzm, dRzp * dRzp) * P.ih2z));
-      const float sTR = fmaf(fmaf(dTxm, dRxm, dTxp * dRxp), P.ih2x,
-                             fmaf(fmaf(dTym, dRym, dTyp * dRyp), P.ih2y,
-                                  fmaf(dTzm, dRzm, dTzp * dRzp) * P.ih2z));
-      const float nT2 = fmaf(0.5f, sTT, P.tau2);
-      const float nR2 = fmaf(0.5f, sRR, P.rho2);
-      const float r1 = fmaf(0.5f, sTR, P.taurho);
-      const float rnT = rsq_norm(nT2), rnR = rsq_norm(nR2);
-      const float c1 = rnT * rnR;
-      const float r = r1 * c1;
+      const float dRzm = -dzR[K1], dRzp = dzR[K];
+      const float tau2 = zc < P.mz ? P.tau2 : __builtin_inff();
+      const float nT2 = fmaf(fmaf(dTxm, dTxm, dTxp * dTxp), P.hhx,
+                             fmaf(fmaf(dTym, dTym, dTyp * dTyp), P.hhy,
+                                  fmaf(fmaf(dTzm, dTzm, dTzp * dTzp), P.hhz, tau2)));
+      const float nR2 = fmaf(fmaf(dRxm, dRxm, dRxp * dRxp), P.hhx,
+                             fmaf(fmaf(dRym, dRym, dRyp * dRyp), P.hhy,
+                                  fmaf(fmaf(dRzm, dRzm, dRzp * dRzp), P.hhz, P.rho2)));
+      const float r1 = fmaf(fmaf(dTxm, dRxm, dTxp * dRxp), P.hhx,
+                            fmaf(fmaf(dTym, dRym, dTyp * dRyp), P.hhy,
+                                 fmaf(fmaf(dTzm, dRzm, dTzp * dRzp), P.hhz, P.taurho)));
       // 1 - r^2 from the float32 sums in float64: in float32 it cancels where r is
-      // close to 1 (aligned images), and the bias of the hardware reciprocal
-      // square root would add up over the voxels of the objective sum
+      // close to 1 (aligned images), and the bias of the hardware reciprocal would
+      // add up over the voxels of the objective sum
       if (MODE != MODE_HV && inB && zc >= zb && zc < ze)
         obj += 1.0 - ((double)r1 * (double)r1) / ((double)nT2 * (double)nR2);
       if constexpr (NEED_C) {
-        const float c2 = r1 * rnT * rnT;
-        const float kx = P.hhx * c1, ky = P.hhy * c1, kz = P.hhz * c1;
-        const float rxm = kx * fmaf(-c2, dTxm, dRxm), rxp = kx * fmaf(-c2, dTxp, dRxp);
-        const float rym = ky * fmaf(-c2, dTym, dRym), ryp = ky * fmaf(-c2, dTyp, dRyp);
-        const float rzm = kz * fmaf(-c2, dTzm, dRzm), rzp = kz * fmaf(-c2, dTzp, dRzp);
-        const float r0 = -(((rxm + rxp) + (rym + ryp)) + (rzm + rzp));
-        float zl;
+        // rows rho-hat(k) = q(k) / (|grad T| |grad R|): every product that leaves the
+        // stage holds two of them, so no square root is formed
+        const float rT = rcp_norm(nT2), rR = rcp_norm(nR2);
+        const float c2 = r1 * rT;
+        const float qxm = P.hhx * fmaf(-c2, dTxm, dRxm), qxp = P.hhx * fmaf(-c2, dTxp, dRxp);
+        const float qym = P.hhy * fmaf(-c2, dTym, dRym), qyp = P.hhy * fmaf(-c2, dTyp, dRyp);
+        const float qzm = P.hhz * fmaf(-c2, dTzm, dRzm), qzp = P.hhz * fmaf(-c2, dTzp, dRzp);
+        const float q0 = -(((qxm + qxp) + (qym + qyp)) + (qzm + qzp));
+        float z;   // z_l times |grad T| |grad R|
         if constexpr (HV) {
-          zl = r0 * av[K1];
-          zl = fmaf(rxm, sA[s1][q - 1], zl);
-          zl = fmaf(rxp, sA[s1][q + 1], zl);
-          zl = fmaf(rym, sA[s1][q - BX], zl);
-          zl = fmaf(ryp, sA[s1][q + BX], zl);
-          zl = fmaf(rzm, av[K2], zl);
-          zl = fmaf(rzp, av[K], zl);
+          z = q0 * av[K1];
+          z = fmaf(qxm, sA[s1][q - 1], z);
+          z = fmaf(qxp, sA[s1][q + 1], z);
+          z = fmaf(qym, sA[s1][q - BX], z);
+          z = fmaf(qyp, sA[s1][q + BX], z);
+          z = fmaf(qzm, av[K2], z);
+          z = fmaf(qzp, av[K], z);
         } else {
-          zl = r;
+          z = r1;
         }
-        zl *= own_row;
-        sE[s1][0][EP + tid] = rxp * zl;
-        sE[s1][1][EP + tid] = rxm * zl;
-        sE[s1][2][EP + tid] = ryp * zl;
-        sE[s1][3][EP + tid] = rym * zl;
-        ezp[K1] = rzp * zl;
-        ezm = rzm * zl;
-        e0[K1] = r0 * zl;
+        const float w = (own_row * rT) * (rR * z);   // (this order: the factors alone may overflow)
+        sE[s1][0][EP + tid] = qxp * w;
+        sE[s1][1][EP + tid] = qxm * w;
+        sE[s1][2][EP + tid] = qyp * w;
+        sE[s1][3][EP + tid] = qym * w;
+        ezp[K1] = qzp * w;
+        ezm = qzm * w;
+        e0[K1] = q0 * w;
       }
     }
 
@@ -500,7 +541,7 @@ __device__ __forceinline__ void tile_body(const TileParams& P, const int bid, co
           }
           KL = cvz.n0;
         }
-        if (inC) {
+        {
           float w = e0[K2];
           if constexpr (!SSD) {
             // rows of the neighbours within the group (beyond its edge: the zero pad,
@@ -513,12 +554,11 @@ __device__ __forceinline__ void tile_body(const TileParams& P, const int bid, co
             w += ezm;
             w += ezp[K];
           }
-          const float wz1 = cvz.f, wz0 = 1.0f - cvz.f;
+          const float w1 = cvz.f * w, w0 = (1.0f - cvz.f) * w;
 #pragma unroll
           for (int d = 0; d < 3; ++d) {
-            const float v = g[K2][d] * w;
-            acc_lo[d] = fmaf(wz0, v, acc_lo[d]);
-            acc_hi[d] = fmaf(wz1, v, acc_hi[d]);
+            acc_lo[d] = fmaf(w0, g[K2][d], acc_lo[d]);
+            acc_hi[d] = fmaf(w1, g[K2][d], acc_hi[d]);
           }
         }
       }
@@ -527,11 +567,14 @@ __device__ __forceinline__ void tile_body(const TileParams& P, const int bid, co
     if constexpr (!SSD) __syncthreads();
   };
 
+  using std::integral_constant;
   issue(tfirst);
-  for (int t = tfirst; t <= tlast; t += 3) {
-    step(std::integral_constant<int, 0>{}, t);
-    if (t + 1 <= tlast) step(std::integral_constant<int, 1>{}, t + 1);
-    if (t + 2 <= tlast) step(std::integral_constant<int, 2>{}, t + 2);
+  step(integral_constant<int, 0>{}, std::true_type{}, tfirst);
+  step(integral_constant<int, 1>{}, std::true_type{}, tfirst + 1);
+  for (int t = tfirst + 2; t <= tlast; t += 3) {
+    step(integral_constant<int, 2>{}, std::false_type{}, t);
+    if (t + 1 <= tlast) step(integral_constant<int, 0>{}, std::false_type{}, t + 1);
+    if (t + 2 <= tlast) step(integral_constant<int, 1>{}, std::false_type{}, t + 2);
   }
 
   if constexpr (NEED_C) {
@@ -542,8 +585,16 @@ __device__ __forceinline__ void tile_body(const TileParams& P, const int bid, co
   if constexpr (MODE != MODE_HV) block_sum_store<NT>(obj, P.red + bid, sRed);
 }
 
+// Bound by vector-instruction issue (about 190 per step and wave, 0.87 of the cycles at
+// 512x512x900 voxels), so the steps hold no instruction that a table, a uniform branch
+// or the order of the factors can save: rows without their common factor 1 / (|grad T|
+// |grad R|), which enters squared and needs no square root; z differences formed
+// once; two lead steps of stage A alone instead of zeroed products.  205 -> 190
+// instructions, Hessian product 512x512x900 1951 -> 1879 us, ten pairs of up to
+// 512x512x136 1866 -> 1825 us; 128 registers (two groups per CU) hold because what is
+// read once per cell lies in LDS.
 template <int BX, int BY, int MODE, bool SSD>
-__global__ __launch_bounds__(BX* BY) void ngf_tile_kernel(const TileParams P, const float* __restrict__ u,
+__global__ __launch_bounds__(BX* BY) __attribute__((amdgpu_waves_per_eu(4))) void ngf_tile_kernel(const TileParams P, const float* __restrict__ u,
                                                           const float* __restrict__ pv) {
   if (P.live && !ld_coherent(P.live)) return;   // a device-steered solve has stopped
   __shared__ TileSmem<BX, BY, MODE, SSD> S;

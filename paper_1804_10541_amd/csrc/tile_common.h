@@ -129,6 +129,21 @@ __device__ __forceinline__ int clamp_m2(int k, int hi) {
   return r;
 }
 
+// max(0, min(k, hi)) for hi >= 0 in one instruction.
+__device__ __forceinline__ int clamp_lo0(int k, int hi) {
+  int r;
+  asm("v_med3_i32 %0, %1, 0, %2" : "=v"(r) : "v"(k), "s"(hi));
+  return r;
+}
+
+// Template coordinate along one axis relative to the voxel-table entry's base cell
+// for its fraction and displacement d, and the coordinate's own fraction.
+__device__ __forceinline__ float template_pos(float f0, float d, float ihT, float& frac) {
+  const float q = __builtin_amdgcn_fmed3f(fmaf(d, ihT, f0), -1.0e7f, 1.0e7f);
+  frac = __builtin_amdgcn_fractf(q);
+  return q;
+}
+
 // Template coordinate along one axis for voxel-table entry s and displacement d:
 // returns the lower template cell and writes the fraction (q - floor(q), at most
 // the float below 1).
@@ -142,6 +157,9 @@ __device__ __forceinline__ int template_cell(const Samp1 s, float d, float ihT, 
 // sums of squares plus tau^2 or rho^2, which the host raises to at least the
 // smallest normal float, so no denormal ever reaches it.
 __device__ __forceinline__ float rsq_norm(float x) { return __builtin_amdgcn_rsqf(x); }
+
+// 1/x by the hardware reciprocal, for the same arguments.
+__device__ __forceinline__ float rcp_norm(float x) { return __builtin_amdgcn_rcpf(x); }
 
 // Buffer descriptor of a raw float array of `bytes` bytes: loads at byte
 // offsets voffset (vector) + soffset (scalar); loads past the end return 0.
