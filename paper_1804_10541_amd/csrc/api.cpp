@@ -817,6 +817,7 @@ mfr_status ctx_init(mfr_ctx* c, const mfr_grid* grid, void* stream, void* ws, si
   HIP_TRY(hipStreamSynchronize(c->stream));
 
   TileParams& p = c->tp;
+  p.zcells2 = cells_follow(cz, true);
   p.live = nullptr;
   p.mx = g.m[0];
   p.my = g.m[1];

@@ -81,6 +81,7 @@ struct TileParams {
   float ih2x, ih2y, ih2z; // 1 / h^2
   float hhx, hhy, hhz;    // 1 / (2 h^2)
   float ihTx, ihTy, ihTz; // 1 / hT
+  int zcells2;            // every cell along z has two voxel planes or more (the image's first and last aside)
   float tau2, rho2, taurho;
   const float* R;         // reference [mz][my][mx]
   const float* Tp;        // padded template [mTz+4][mTy+4][mTx+4]

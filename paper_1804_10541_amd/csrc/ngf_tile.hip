@@ -81,6 +81,13 @@ struct TileSmem {
   // u and p of the own column at the upper one of the two node planes in use (own
   // slot only): read when the march passes to the next node plane, not kept in registers
   float sHi[HV ? 6 : 3][NT];
+  // Node values of the block, one node plane ahead of the march (u's, then p's), and
+  // where this thread's two of a component set lie in a node plane.  Not for SSD, whose
+  // steps hold no barrier, nor where a CU would lose its second group (the LDS of 64 x 8
+  // columns) or registers spill (the gradient of 1024 columns).
+  static constexpr bool STG = !SSD && (NT > 512 ? HV : BX == 32);
+  float sN[HV ? 2 : 1][STG ? 2 * NT : 1];
+  unsigned sSrc[2][STG ? NT : 1];
   // z conversion and template-coordinate entries of planes zb-2 .. ze+1 (clamped
   // into the image): read at a uniform index every plane, from LDS rather than
   // through a vector load whose latency would sit on every step's address path
@@ -342,6 +349,57 @@ __device__ __forceinline__ void tile_body(const TileParams& P, const int bid, co
       o[d] = fmaf(wy1, hi, wy0 * lo);
     }
   };
+  // The next node plane through LDS: loaded when the march enters a cell, written to
+  // LDS in the step behind (the loads precede that step's template loads, which it
+  // waits for anyway), read when it enters the next cell.  Cells of two planes or more
+  // (P.zcells2), so a barrier lies between each two of these; the loads' latency, which
+  // every wave of the group would meet at the same step, is hidden.
+  const int nn = nxl * nyl;
+  // (a march of fewer than four cells has too little of it to hide for the set-up)
+  const bool staged =
+      Sm::STG && P.zcells2 && 3 * nn <= 2 * NT && P.cz[min(ze + 1, P.mz - 1)].n0 - P.cz[max(zb - 2, 0)].n0 >= 4;
+  float stu[2] = {0.f, 0.f}, stp[2] = {0.f, 0.f};
+  bool pending = false;
+  auto stage_load = [&](int k) {
+    if (k >= P.nz) return;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      if (tid + i * NT < 3 * nn) {
+        const unsigned q = S.sSrc[i][tid] + (unsigned)k * nxy;
+        stu[i] = ld32(u, q);
+        if (HV) stp[i] = ld32(pv, q);
+      }
+    pending = true;
+  };
+  auto stage_store = [&]() {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      if (tid + i * NT < 3 * nn) {
+        S.sN[0][tid + i * NT] = stu[i];
+        if (HV) S.sN[HV ? 1 : 0][tid + i * NT] = stp[i];
+      }
+    pending = false;
+  };
+  auto staged_interp = [&](const float* f, const Conv1 cvx, const Conv1 cvy, float (&o)[3]) {
+    const float wx0 = 1.0f - cvx.f, wx1 = cvx.f, wy0 = 1.0f - cvy.f, wy1 = cvy.f;
+    const float* q = f + (cvy.n0 - noy) * nxl + (cvx.n0 - nox);
+#pragma unroll
+    for (int d = 0; d < 3; ++d, q += nn) {
+      const float lo = fmaf(wx1, q[1], wx0 * q[0]);
+      const float hi = fmaf(wx1, q[nxl + 1], wx0 * q[nxl]);
+      o[d] = fmaf(wy1, hi, wy0 * lo);
+    }
+  };
+  if constexpr (Sm::STG)
+    if (staged) {
+      for (int i = 0; i < 2; ++i) {
+        const int e = tid + i * NT, d = e / nn, r = e - d * nn, row = r / nxl;
+        S.sSrc[i][tid] = (unsigned)d * nb + (unsigned)((noy + row) * P.nx + nox + r - row * nxl);
+      }
+      stage_load(P.cz[max(zb - 2, 0)].n0 + 2);
+      if (pending) stage_store();
+      __syncthreads();
+    }
 
   // Stage A inputs of the next plane, loaded one step ahead.
   float nx_t[8];
@@ -357,7 +415,9 @@ __device__ __forceinline__ void tile_body(const TileParams& P, const int bid, co
       int ct = tid;   // (opaque, so that nothing of the column's weights is kept over the march)
       asm volatile("" : "+v"(ct));
       const Conv1 cvx = sCx[ct % BX], cvy = sCy[ct / BX];
-      if (cvz.n0 == Kp + 1) {
+      float uhi[3], phi[3];
+      bool next = cvz.n0 == Kp + 1;
+      if (next) {
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
           ulo[d] = S.sHi[d][ct];
@@ -367,9 +427,14 @@ __device__ __forceinline__ void tile_body(const TileParams& P, const int bid, co
         xy_interp(u, cvz.n0, cvx, cvy, ulo);
         if (HV) xy_interp(pv, cvz.n0, cvx, cvy, plo);
       }
-      float uhi[3], phi[3];
-      xy_interp(u, cvz.n0 + 1, cvx, cvy, uhi);
-      if (HV) xy_interp(pv, cvz.n0 + 1, cvx, cvy, phi);
+      if (Sm::STG && staged && next) {
+        staged_interp(S.sN[0], cvx, cvy, uhi);
+        if (HV) staged_interp(S.sN[HV ? 1 : 0], cvx, cvy, phi);
+        stage_load(cvz.n0 + 2);
+      } else {
+        xy_interp(u, cvz.n0 + 1, cvx, cvy, uhi);
+        if (HV) xy_interp(pv, cvz.n0 + 1, cvx, cvy, phi);
+      }
 #pragma unroll
       for (int d = 0; d < 3; ++d) {
         S.sHi[d][ct] = uhi[d];
@@ -424,6 +489,8 @@ __device__ __forceinline__ void tile_body(const TileParams& P, const int bid, co
     constexpr int K = decltype(Kc)::value;   // slot of plane t
     constexpr int K1 = (K + 2) % 3;          // slot of plane t-1
     constexpr int K2 = (K + 1) % 3;          // slot of plane t-2
+
+    if (Sm::STG && pending) stage_store();
 
     // ---------------- stage A: plane t ----------------
     {
@@ -593,6 +660,10 @@ __device__ __forceinline__ void tile_body(const TileParams& P, const int bid, co
 // instructions, Hessian product 512x512x900 1951 -> 1879 us, ten pairs of up to
 // 512x512x136 1866 -> 1825 us; 128 registers (two groups per CU) hold because what is
 // read once per cell lies in LDS.
+// Node values through LDS a node plane ahead: 24 loads per cell, column and wave, whose
+// latency all waves of a group met at the same step, become one or two per thread:
+// 1879 -> 1800 us, ten pairs 1825 -> 1765 us (8-byte loads of node pairs instead: 2075
+// us; the template's corner pairs as 4-byte loads: 1947 us).
 template <int BX, int BY, int MODE, bool SSD>
 __global__ __launch_bounds__(BX* BY) __attribute__((amdgpu_waves_per_eu(4))) void ngf_tile_kernel(const TileParams P, const float* __restrict__ u,
                                                           const float* __restrict__ pv) {
