@@ -1015,18 +1015,14 @@ hipEvent_t prof_event(mfr_ctx* c) {
 hipError_t enqueue_diag(mfr_ctx* c, const float* u, float* diag) {
   if (c->geo.dim == 2)
     return c->tiling.dg.on ? launch_diag_tile(c->dtp, u, diag, c->stream) : launch_plane_jacobi(c->dp, u, diag, c->stream);
-  if (c->tiling.dg.on) return launch_diag_tile(c->dtp, u, diag, c->stream);
+  // With a learned preconditioner bound, one order of summation whatever split and
+  // kernel the diagonal takes otherwise: its network rounds the diagonal to 16 bits, so
+  // the last bit of a sum can change an activation by 2^-9 (outputs 2e-3 of their
+  // size apart with another z split alone, on half of the inputs tried).  Every caller
+  // of such a context gets the same bits (a network of zeros is exactly Jacobi).
+  if (c->tiling.dg.on) return launch_diag_tile(c->bound_pcs.empty() ? c->dtp : c->dtn, u, diag, c->stream);
   if (c->jac_tiled) return launch_jacobi_tile(c->jp, u, diag, c->stream);
   return launch_jacobi_diag(c->dp, u, diag, c->stream);
-}
-
-// The diagonal as input of the learned preconditioner, summed in one order whatever
-// kernel and split are taken for the diagonal itself: the network rounds its inputs
-// to 16 bits, so a last bit of a sum can change an activation by 2^-9 (outputs 2e-3
-// of their size apart with another z split alone, on half of the inputs tried).
-hipError_t enqueue_diag_network(mfr_ctx* c, const float* u, float* diag) {
-  if (c->geo.dim == 2 || !c->tiling.dg.on) return enqueue_diag(c, u, diag);
-  return launch_diag_tile(c->dtn, u, diag, c->stream);
 }
 
 // The Jacobi preconditioner of a CG solve: the exact diagonal with zero entries

@@ -581,7 +581,7 @@ __device__ __forceinline__ void tile_body(const TileParams& P, const int bid, co
         } else {
           z = r1;
         }
-        const float w = (own_row * rT) * (rR * z);   // (this order: the factors alone may overflow)
+        const float w = own_row * (rR * (rT * z));   // (this order: the factors alone may overflow)
         sE[s1][0][EP + tid] = qxp * w;
         sE[s1][1][EP + tid] = qxm * w;
         sE[s1][2][EP + tid] = qyp * w;
