@@ -139,6 +139,10 @@ struct mfr_ctx {
   mfr::Layout lay;
   hipStream_t stream;
   char* ws;
+  // Results that a synchronous call returns, written by the device itself (pinned;
+  // null: copied instead).  The capturable entry points never touch it: a graph may
+  // outlive the context.
+  mfr::HostPage* host = nullptr;
   const float* R;
   bool have_images;
   mfr::TileParams tp;
@@ -217,9 +221,10 @@ hipError_t enqueue_pcg_diag(mfr_ctx* c, const float* u, float* diag);   // zero 
 int node_blocks(const mfr_ctx* c);   // work-groups of a node pass
 int node_parts(const mfr_ctx* c);    // float64 partials of a gradient / Hv node pass (one per group)
 mfr_status check_ptr(const void* p, const char* name);
-mfr_status enqueue_objective(mfr_ctx* c, const float* u);
+// to_host: the sums go to c->host as well, for read_objective
+mfr_status enqueue_objective(mfr_ctx* c, const float* u, bool to_host = false);
 mfr_status read_objective(mfr_ctx* c, double* J, double* D, double* S);
-mfr_status enqueue_gradient(mfr_ctx* c, const float* u, float* g);
+mfr_status enqueue_gradient(mfr_ctx* c, const float* u, float* g, bool to_host = false);
 mfr_status enqueue_hess_vec(mfr_ctx* c, const float* u, const float* p, float* q);
 mfr_status pcg_run(mfr_ctx* c, const float* u, const float* b, float* s_out, const mfr_pcg_opts* o,
                    mfr_pcg_info* info);

@@ -125,7 +125,7 @@ mfr_status lbfgs_run(mfr_ctx* c, float* u, const mfr_lbfgs_opts* o, char* work, 
 
   mfr_lbfgs_report R{};
   double J = 0.0;
-  MFR_TRY(enqueue_gradient(c, u, g));
+  MFR_TRY(enqueue_gradient(c, u, g, true));
   MFR_TRY(read_objective(c, &J, nullptr, nullptr));
   R.J_initial = R.J_final = J;
   R.evals = 1;
@@ -160,7 +160,7 @@ mfr_status lbfgs_run(mfr_ctx* c, float* u, const mfr_lbfgs_opts* o, char* work, 
     bool accepted = false;
     for (int ls = 0; ls < o->armijo_max; ++ls) {
       HIP_TRY(launch_axpy(n3, u, (float)eta, d, trial, c->stream));
-      MFR_TRY(enqueue_objective(c, trial));
+      MFR_TRY(enqueue_objective(c, trial, true));
       const mfr_status st = read_objective(c, &Jn, nullptr, nullptr);
       ++R.evals;
       if (st == MFR_OK && Jn <= J + o->armijo_c1 * eta * slope) {
@@ -178,7 +178,7 @@ mfr_status lbfgs_run(mfr_ctx* c, float* u, const mfr_lbfgs_opts* o, char* work, 
     while (std::find(hist.begin(), hist.end(), slot) != hist.end()) ++slot;
     HIP_TRY(launch_axpy(n3, trial, -1.0f, u, S[slot], c->stream));   // s = u_new - u (the step taken)
     HIP_TRY(hipMemcpyAsync(u, trial, sizeof(float) * n3, hipMemcpyDeviceToDevice, c->stream));
-    MFR_TRY(enqueue_gradient(c, u, gn));
+    MFR_TRY(enqueue_gradient(c, u, gn, true));
     MFR_TRY(read_objective(c, &J, nullptr, nullptr));
     ++R.evals;
     HIP_TRY(launch_axpy(n3, gn, -1.0f, g, Y[slot], c->stream));     // y = g_new - g

@@ -280,7 +280,8 @@ hipError_t launch_tile_batch(const TileShape& s, int mode, const BatchJobs& j, h
 hipError_t launch_node_pass(int mode, const NodeParams& q, const float* f, float* out, int blocks,
                             hipStream_t st);
 hipError_t launch_sum(const double* parts, int n, double* out, hipStream_t st);
-hipError_t launch_sum2(const double* a, int na, const double* b, int nb, double* out, hipStream_t st);   // into out[0], out[1]
+// sums of a and b into out[0], out[1] and, if host is not null, also there
+hipError_t launch_sum2(const double* a, int na, const double* b, int nb, double* out, double* host, hipStream_t st);
 // bz: zero border along z (2; 0 for a two-dimensional template, mz = 1)
 hipError_t launch_pad_template(const float* T, float* Tp, int mx, int my, int mz, int bz, hipStream_t st);
 // Two-dimensional problems (plane_tile.hip): the fused tile kernel and the exact
@@ -318,6 +319,14 @@ enum PcgSlot : int {
   SC_D = 8, SC_S = 9, SC_J = 10, SC_DOT = 11, SC_RELRES = 12, SC_RTOL = 13, SC_ZR = 14, SC_ZRP = 15,
   SC_COUNT = 16
 };
+
+// What a synchronous solve reads back, in host memory that the device can write.
+struct HostPage {
+  double obj[2];       // the two sums of an objective or gradient
+  double sc[SC_COUNT];
+  int ctrl[1 + ST_COUNT];
+};
+hipError_t launch_publish(const double* sc, const int* ctrl, HostPage* host, hipStream_t st);
 // zero entries of a Jacobi diagonal -> 1 (the preconditioner leaves them unscaled)
 hipError_t launch_safe_diag(int n3, float* d, hipStream_t st);
 hipError_t launch_pcg_init(int n3, const float* b, const float* diag, float* s, float* r, float* z,

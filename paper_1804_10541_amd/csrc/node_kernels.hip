@@ -371,10 +371,24 @@ __global__ __launch_bounds__(1024) void sum_kernel(const double* __restrict__ pa
 
 // Two sums in one launch: a into out[0], b into out[1].
 __global__ __launch_bounds__(1024) void sum2_kernel(const double* __restrict__ a, int na, const double* __restrict__ b,
-                                                    int nb, double* __restrict__ out) {
+                                                    int nb, double* __restrict__ out, double* __restrict__ host) {
   __shared__ double sred[16];
   const double s = blockIdx.x == 0 ? sum_group(a, na, sred) : sum_group(b, nb, sred);
-  if (threadIdx.x == 0) out[blockIdx.x] = s;
+  if (threadIdx.x == 0) {
+    out[blockIdx.x] = s;
+    if (host) host[blockIdx.x] = s;
+  }
+}
+
+__global__ void publish_kernel(const double* __restrict__ sc, const int* __restrict__ ctrl, HostPage* __restrict__ h) {
+  const int t = threadIdx.x;
+  if (t < SC_COUNT) h->sc[t] = sc[t];
+  if (t < 1 + ST_COUNT) h->ctrl[t] = ctrl[t];
+}
+
+hipError_t launch_publish(const double* sc, const int* ctrl, HostPage* host, hipStream_t st) {
+  hipLaunchKernelGGL(publish_kernel, dim3(1), dim3(64), 0, st, sc, ctrl, host);
+  return hipGetLastError();
 }
 
 hipError_t launch_sum(const double* parts, int n, double* out, hipStream_t st) {
@@ -382,8 +396,8 @@ hipError_t launch_sum(const double* parts, int n, double* out, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_sum2(const double* a, int na, const double* b, int nb, double* out, hipStream_t st) {
-  hipLaunchKernelGGL(sum2_kernel, dim3(2), dim3(1024), 0, st, a, na, b, nb, out);
+hipError_t launch_sum2(const double* a, int na, const double* b, int nb, double* out, double* host, hipStream_t st) {
+  hipLaunchKernelGGL(sum2_kernel, dim3(2), dim3(1024), 0, st, a, na, b, nb, out, host);
   return hipGetLastError();
 }
 
