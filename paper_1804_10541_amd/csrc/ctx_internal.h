@@ -237,7 +237,7 @@ mfr_status pc_begin_solve(mfr_pc* pc, const float* diag);
 // needs it for the first layer's weight gradient).
 mfr_status pc_forward(mfr_pc* pc, const float* r, const float* diag, float* z, bool scales_ready = false,
                       const float* rprev = nullptr, double* zred = nullptr, const int* live = nullptr,
-                      bool keep_input = false);
+                      bool keep_input = false, bool diag_scale = false);
 float* pc_scratch_vec(mfr_pc* pc);
 // The context of pc is being destroyed: pc is left unbound (mfr_pc_bind again before use).
 void pc_release_context(mfr_pc* pc);

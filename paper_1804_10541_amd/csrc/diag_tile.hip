@@ -1264,31 +1264,61 @@ __global__ __launch_bounds__(kPlaneNT) void plane_diag_kernel(const DiagTilePara
 // node n (fixed order), scaled, plus the regulariser's diagonal:
 // curvature (L^T L)_nn = L_nn^2 + sum over present neighbours of 1/hy^4,
 // diffusive -L_nn, elastic -L_nn + kappa (adjacent cells) / (16 hy_d^2).
+// A thread sums the NC components of a node: up to two groups meet it along an axis,
+// whose partials are then loaded together (any number one after the other).  Bound by
+// the latency of that load behind two of tables: 65x65x49 nodes 12 -> 6 us,
+// 129x129x33 22 -> 13 us against a thread per component and one load at a time.
+template <int NC>
 __global__ __launch_bounds__(256) void diag_node_kernel(const DiagTileParams D, float* __restrict__ diag) {
   const TileParams& P = D.t;
-  const int n = blockIdx.x * 256 + threadIdx.x, d = blockIdx.y;
+  const int n = blockIdx.x * 256 + threadIdx.x;
   if (n >= P.nbar) return;
   const int i = n % P.nx, j = (n / P.nx) % P.ny, k = n / (P.nx * P.ny);
   const Range1 rx = D.ntx[i], ry = D.nty[j], rz = D.ntz[k];
-  float s = 0.0f;
-  for (int cz = rz.lo; cz <= rz.hi; ++cz) {
-    const int kz = k - D.orgz[cz];
-    for (int cy = ry.lo; cy <= ry.hi; ++cy) {
-      const int iy = j - D.orgy[cy];
-      for (int cx = rx.lo; cx <= rx.hi; ++cx) {
-        const int jx = i - D.orgx[cx];
-        const size_t slot = (size_t)cx + (size_t)P.tiles_x * ((size_t)cy + (size_t)P.tiles_y * cz);
-        s += P.part[(((slot * 3 + d) * P.nzt + kz) * P.nyt + iy) * P.nxt + jx];
-      }
+  const size_t dstride = (size_t)P.nzt * P.nyt * P.nxt;
+  // offset of the node in the block of group (cx, cy, cz), first component
+  auto place = [&](int cx, int ox, int cy, int oy, int cz, int oz) {
+    const size_t slot = (size_t)cx + (size_t)P.tiles_x * ((size_t)cy + (size_t)P.tiles_y * cz);
+    return slot * 3 * dstride + ((size_t)(k - oz) * P.nyt + (j - oy)) * P.nxt + (i - ox);
+  };
+  float s[NC];
+#pragma unroll
+  for (int d = 0; d < NC; ++d) s[d] = 0.0f;
+  if (rx.hi - rx.lo < 2 && ry.hi - ry.lo < 2 && rz.hi - rz.lo < 2) {
+    const int ox[2] = {D.orgx[rx.lo], D.orgx[rx.hi]}, oy[2] = {D.orgy[ry.lo], D.orgy[ry.hi]};
+    const int oz[2] = {D.orgz[rz.lo], D.orgz[rz.hi]};
+    float v[8][NC];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int ax = q & 1, ay = (q >> 1) & 1, az = q >> 2;
+      const bool in = rx.lo + ax <= rx.hi && ry.lo + ay <= ry.hi && rz.lo + az <= rz.hi;
+      const size_t o = in ? place(rx.lo + ax, ox[ax], ry.lo + ay, oy[ay], rz.lo + az, oz[az]) : 0;
+#pragma unroll
+      for (int d = 0; d < NC; ++d) v[q][d] = in ? P.part[o + d * dstride] : 0.0f;
     }
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+#pragma unroll
+      for (int d = 0; d < NC; ++d) s[d] += v[q][d];
+  } else {
+    for (int cz = rz.lo; cz <= rz.hi; ++cz)
+      for (int cy = ry.lo; cy <= ry.hi; ++cy)
+        for (int cx = rx.lo; cx <= rx.hi; ++cx) {
+          const size_t o = place(cx, D.orgx[cx], cy, D.orgy[cy], cz, D.orgz[cz]);
+#pragma unroll
+          for (int d = 0; d < NC; ++d) s[d] += P.part[o + d * dstride];
+        }
   }
   const int cxn = (i > 0) + (i < P.nx - 1), cyn = (j > 0) + (j < P.ny - 1), czn = (k > 0) + (k < P.nz - 1);
   const float Lnn = -(cxn * D.ihy2x + cyn * D.ihy2y + czn * D.ihy2z);
   const float LL =
       P.reg ? -Lnn : Lnn * Lnn + cxn * D.ihy2x * D.ihy2x + cyn * D.ihy2y * D.ihy2y + czn * D.ihy2z * D.ihy2z;
   const float ncell = P.reg == 2 ? P.kappa * (float)(cxn * cyn * czn) * 0.0625f : 0.0f;
-  const float ih2 = d == 0 ? D.ihy2x : d == 1 ? D.ihy2y : D.ihy2z;
-  diag[(size_t)d * P.nbar + n] = fmaf(D.s_ngf, s, D.s_curv * fmaf(ncell, ih2, LL));
+#pragma unroll
+  for (int d = 0; d < NC; ++d) {
+    const float ih2 = d == 0 ? D.ihy2x : d == 1 ? D.ihy2y : D.ihy2z;
+    diag[(size_t)d * P.nbar + n] = fmaf(D.s_ngf, s[d], D.s_curv * fmaf(ncell, ih2, LL));
+  }
 }
 
 hipError_t launch_diag_tile(const DiagTileParams& d, const float* u, float* diag, hipStream_t st) {
@@ -1297,7 +1327,7 @@ hipError_t launch_diag_tile(const DiagTileParams& d, const float* u, float* diag
     hipLaunchKernelGGL(plane_diag_kernel, dim3(grid), dim3(kPlaneNT), 0, st, d, u);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(diag_node_kernel, dim3((d.t.nbar + 255) / 256, 2), dim3(256), 0, st, d, diag);
+    hipLaunchKernelGGL(diag_node_kernel<2>, dim3((d.t.nbar + 255) / 256), dim3(256), 0, st, d, diag);
     return hipGetLastError();
   }
   const dim3 blk(kDiagBX * kDiagBY);
@@ -1313,7 +1343,7 @@ hipError_t launch_diag_tile(const DiagTileParams& d, const float* u, float* diag
     hipLaunchKernelGGL((diag_tile_kernel<false>), dim3(grid), blk, 0, st, d, u);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(diag_node_kernel, dim3((d.t.nbar + 255) / 256, 3), dim3(256), 0, st, d, diag);
+  hipLaunchKernelGGL(diag_node_kernel<3>, dim3((d.t.nbar + 255) / 256), dim3(256), 0, st, d, diag);
   return hipGetLastError();
 }
 

@@ -256,9 +256,12 @@ mfr_status pc_begin_solve(mfr_pc* pc, const float* diag) {
 
 // z = r / diag + rms(r / diag) * CNN(features)[0..2].  scales_ready: the RMS of
 // r and r/diag are already in the scalars (the flexible-CG update computes them).
+// diag_scale: the RMS of the diagonal is formed with them (one launch of sums and one
+// that finishes them instead of two each: 189 -> 176 us with the node sums of the diagonal for an application at 65x65x49
+// nodes), where pc_begin_solve has not.
 // zred: the final layer also leaves per-group partials of z.r and z.rprev there.
 mfr_status pc_forward(mfr_pc* pc, const float* r, const float* diag, float* z, bool scales_ready,
-                      const float* rprev, double* zred, const int* live, bool keep_input) {
+                      const float* rprev, double* zred, const int* live, bool keep_input, bool diag_scale) {
   hipStream_t st = st_of(pc);
   if (!scales_ready) {
     DotsArgs d{};
@@ -272,6 +275,12 @@ mfr_status pc_forward(mfr_pc* pc, const float* r, const float* diag, float* z, b
     o.out[0] = pc->sc + PC_RMS_Y;
     o.out[1] = pc->sc + PC_RMS_R;
     o.rms_scale[0] = o.rms_scale[1] = 1.0 / pc->n3;
+    if (diag_scale) {
+      d.count = 3;
+      d.a[2] = diag;
+      o.out[2] = pc->sc + PC_RMS_D;
+      o.rms_scale[2] = 1.0 / pc->n3;
+    }
     HIP_TRY(launch_pc_dots(d, o, pc->red, st));
   }
   // the network (timed as one record when the context's timing is on)
@@ -502,8 +511,8 @@ mfr_status mfr_pc_apply(mfr_pc* pc, const float* u, const float* r, float* z) {
   MFR_TRY(check_ptr(z, "z"));
   if (z == r || z == u) return fail(MFR_EINVAL, "z must not alias u or r");
   HIP_TRY(enqueue_diag(pc->c, u, pc->diag));
-  MFR_TRY(pc_begin_solve(pc, pc->diag));
-  return pc_forward(pc, r, pc->diag, z);
+  MFR_TRY(refresh_gR(pc));
+  return pc_forward(pc, r, pc->diag, z, false, nullptr, nullptr, nullptr, false, true);
 }
 
 mfr_status mfr_pc_train_system(mfr_pc* pc, const float* u, const float* b, const mfr_pc_train_opts* o,

@@ -71,16 +71,15 @@ __global__ __launch_bounds__(kPB) void pc_dots_kernel(const DotsArgs d, double* 
 
 // out[k] = sum_b red[k * blocks + b] (fixed order); sqrt_scale[k] > 0 stores
 // sqrt(sum * sqrt_scale[k]) instead (an RMS).
-__global__ __launch_bounds__(256) void pc_dots_finish_kernel(const double* __restrict__ red, int blocks, int count,
+__global__ __launch_bounds__(256) void pc_dots_finish_kernel(const double* __restrict__ red, int blocks,
                                                              DotsOut o, const int* live) {
   if (live && !ld_coherent(live)) return;
   __shared__ double sred[4];
-  for (int k = 0; k < count; ++k) {
-    double a = 0.0;
-    for (int b = threadIdx.x; b < blocks; b += 256) a += red[(size_t)k * blocks + b];
-    const double s = block_sum256(a, sred);
-    if (threadIdx.x == 0 && o.out[k]) *o.out[k] = o.rms_scale[k] > 0.0 ? sqrt(s * o.rms_scale[k]) : s;
-  }
+  const int k = blockIdx.x;
+  double a = 0.0;
+  for (int b = threadIdx.x; b < blocks; b += 256) a += red[(size_t)k * blocks + b];
+  const double s = block_sum256(a, sred);
+  if (threadIdx.x == 0 && o.out[k]) *o.out[k] = o.rms_scale[k] > 0.0 ? sqrt(s * o.rms_scale[k]) : s;
 }
 
 int pc_dots_blocks(size_t n) { return vec_blocks_for(n); }
@@ -90,7 +89,7 @@ hipError_t launch_pc_dots(const DotsArgs& d, const DotsOut& o, double* red, hipS
   hipLaunchKernelGGL(pc_dots_kernel, dim3(blocks), dim3(kPB), 0, st, d, red);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(pc_dots_finish_kernel, dim3(1), dim3(256), 0, st, red, blocks, d.count, o, d.live);
+  hipLaunchKernelGGL(pc_dots_finish_kernel, dim3(d.count), dim3(256), 0, st, red, blocks, o, d.live);
   return hipGetLastError();
 }
 
