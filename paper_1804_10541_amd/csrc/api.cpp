@@ -233,9 +233,9 @@ static int most_chunks(const std::vector<Conv1>& c, int n, int len) {
 // Chunks of a march over `planes` planes by xy column blocks, each chunk costing
 // its planes plus `lead` planes of lead-in: the number of chunks (of min_len to
 // max_len planes) with the least estimated time on 256 CUs.  A CU holds per_cu
-// groups at once; where it holds a single one of two, that one advances
-// faster, by solo.  Rounds of 256 per_cu groups follow each other; a last round
-// of at most one group per CU costs solo of a full one.  Measured with the
+// groups at once; where it holds fewer, these advance faster: a round of
+// one group per CU costs solo of a full one, and linearly more for more.  Rounds of
+// 256 per_cu groups follow each other, the last one with what is left.  Measured with the
 // Hessian product (32 x 16 columns, two groups per CU, solo 0.7, lead-in 4): 6
 // chunks instead of 4 at 512x512x900 1959 -> 1847 us, 10 of 10 planes instead of 6
 // of 16 at 128x128x96 49 -> 38 us, 8 of 4 instead of 2 of 16 at 32^3 35 -> 17 us
@@ -249,7 +249,9 @@ static int pick_chunks(long long xy, int planes, int min_len, int max_len, int p
     const int len = (planes + c - 1) / c;
     const long long groups = xy * ((planes + len - 1) / len);
     const long long full = groups / slots, rem = groups % slots;
-    const double rounds = (double)full + (rem == 0 ? 0.0 : rem <= 256 && per_cu > 1 ? solo : 1.0);
+    const long long held = (rem + 255) / 256;   // groups per CU in the last round
+    const double last = per_cu > 1 ? solo + (1.0 - solo) * (double)(held - 1) / (per_cu - 1) : 1.0;
+    const double rounds = (double)full + (rem == 0 ? 0.0 : last);
     const double t = rounds * (len + lead);
     if (best_t == 0.0 || t < 0.99 * best_t) {   // (ties: fewer, longer chunks)
       best_t = t;
@@ -285,16 +287,25 @@ static bool weights_clear(const std::vector<Conv1>& c) {
   return true;
 }
 
-static Tiling make_tiling_plane(const Geo& g, const std::vector<Conv1>& cx, const std::vector<Conv1>& cy) {
+static Tiling make_tiling_plane(const Geo& g, const std::vector<Conv1>& cx, const std::vector<Conv1>& cy, bool compact) {
   Tiling t;
   const mfr_tile_config cfg = current_tile_config();
   t.shape = TileShape{kPlaneNT, 1};
   const int TX = kPlaneNT - 2;
   t.tiles_x = (g.m[0] + TX - 1) / TX;
   t.tiles_y = 1;
-  const int target = cfg.target_groups > 0 ? cfg.target_groups : 2048;
-  int chunks = std::max(1, (target + t.tiles_x - 1) / t.tiles_x);
-  chunks = std::min(chunks, std::max(1, g.m[1] / 16));
+  int chunks;
+  if (cfg.target_groups > 0 || compact) {   // a given number of groups, chunks of at least 16 rows
+    const int target = cfg.target_groups > 0 ? cfg.target_groups : 2048;
+    chunks = std::max(1, (target + t.tiles_x - 1) / t.tiles_x);
+    chunks = std::min(chunks, std::max(1, g.m[1] / 16));
+  } else {
+    // six groups per CU (registers), one alone 0.52 of their time, lead-in 4 rows.
+    // Measured with the gradient: 4096 x 4096 in 90 chunks of 46 rows 78 us (121 of
+    // 34, a round and a third: 96 us), 1024 x 1024 in chunks of 4 rows 16 us (of 16:
+    // 23 us), 256 x 256 12 us (21 us)
+    chunks = pick_chunks(t.tiles_x, g.m[1], 4, kMaxChunk, 6, 4.0, 0.52);
+  }
   int clen = (g.m[1] + chunks - 1) / chunks;
   if (cfg.chunk_len > 0) clen = cfg.chunk_len;
   t.chunk_len = std::min(std::min(clen, g.m[1]), kMaxChunk);
@@ -362,7 +373,7 @@ static DiagTiling diag_tiling(const Geo& g, const std::vector<Conv1>& cx, const 
 
 Tiling make_tiling(const Geo& g, const std::vector<Conv1>& cx, const std::vector<Conv1>& cy,
                    const std::vector<Conv1>& cz, bool compact) {
-  if (g.dim == 2) return make_tiling_plane(g, cx, cy);
+  if (g.dim == 2) return make_tiling_plane(g, cx, cy, compact);
   Tiling t;
   const mfr_tile_config cfg = current_tile_config();
   t.shape = TileShape{cfg.bx, cfg.by};
