@@ -264,8 +264,14 @@ static int pick_chunks(long long xy, int planes, int min_len, int max_len, int p
 // The least chunk length, from 4 planes on, with at most two chunks holding one
 // node plane, so that the partial slots of P^T along the march stay at two.
 static int min_chunk(const std::vector<Conv1>& c, int n) {
+  const std::vector<Range1> cols = node_cols(c, n);
+  auto over = [&](int len) {
+    for (const Range1& r : cols)
+      if (r.hi / len - r.lo / len > 1) return true;
+    return false;
+  };
   int len = 4;
-  while (len < (int)c.size() && most_chunks(c, n, len) > 2) ++len;
+  while (len < (int)c.size() && over(len)) ++len;
   return len;
 }
 
@@ -487,7 +493,7 @@ Layout make_layout(const Geo& g, const Tiling& t) {
   L.red_tile = take(sizeof(double) * (size_t)t.grid());
   // node-pass partials (one per group) and those of the other vector kernels
   L.red_node = take(sizeof(double) * std::max(node_groups(g.nbar), 2 * 1024));
-  L.red_vec = take(sizeof(double) * 2 * 1024);       // partials of the CG vector kernels (two per group)
+  L.red_vec = take(sizeof(double) * 2 * std::min<size_t>((nc * g.nbar + kVecBlock - 1) / kVecBlock, 1024));   // of the CG vector kernels (two per group)
   L.sc = take(sizeof(double) * SC_COUNT);
   L.vec = take(sizeof(float) * nc * g.nbar * 8);   // PCG r z p q diag; GN rhs, trial, direction
   L.div = take(sizeof(float) * g.nbar);           // elastic: divergence per cell of the nodal grid
@@ -519,6 +525,10 @@ static mfr_status ctx_init_plane(mfr_ctx* c, void* stream, void* ws, size_t ws_b
   auto cy = conv_table(g.m[1], g.n[1]);
   c->tiling = make_tiling(g, cx, cy, cy);
   c->lay = make_layout(g, c->tiling);
+  if (ws_bytes < c->lay.total) {   // longer chunks, fewer partials
+    c->tiling = make_tiling(g, cx, cy, cy, true);
+    c->lay = make_layout(g, c->tiling);
+  }
   if (!ws) return fail(MFR_EINVAL, "workspace is NULL");
   if (reinterpret_cast<uintptr_t>(ws) % 256 != 0) return fail(MFR_EINVAL, "workspace must be 256-byte aligned");
   if (ws_bytes < c->lay.total)

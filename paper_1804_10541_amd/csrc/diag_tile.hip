@@ -556,8 +556,8 @@ __device__ __forceinline__ NodeCols node_columns(const Conv1* c, int B, int firs
 //
 // Bound by vector-instruction issue (about 340 per row plane and wave).  The
 // diagonal with its node pass, gather -> march (NGF; SSD): 512x512x128 voxels,
-// 129x129x33 nodes 894 -> 523 us (SSD 480 -> 207), 257x257x65 nodes 1290 -> 815 us,
-// 128x128x96, 65x65x49 nodes 97 -> 72 us.
+// 129x129x33 nodes 894 -> 510 us (SSD 480 -> 202), 257x257x65 nodes 1290 -> 740 us,
+// 128x128x96, 65x65x49 nodes 97 -> 65 us.
 template <bool SSD, bool SCALED>
 __global__ __launch_bounds__(kDiagBX* kDiagBY) __attribute__((amdgpu_waves_per_eu(4))) void diag_march_kernel(
     const DiagTileParams D, const float* __restrict__ u) {

@@ -2,10 +2,14 @@
 which the other tests hold against the float64 oracle, for images of one and more x tiles, fewer rows
 than a chunk and node rows that three chunks hold.  Tolerance 2e-6 (relative L2; float32 sums in
 another order, sqrt of the term count), the objective 1e-6."""
+import ctypes
+
 import pytest
+import torch
 
 from gpu_cases import DEV, rel_l2, to_dev
 from paper_1804_10541_amd import mfr
+from synth import GridSpec
 from test_gpu_plane import plane_case
 
 pytestmark = pytest.mark.gpu
@@ -33,3 +37,17 @@ def test_derived_rows(m, my):
         assert abs(o[0] - out[0][0]) <= 1e-6 * abs(out[0][0])
         for a, b in zip(o[1:], out[0][1:]):
             assert rel_l2(a, b) <= 2e-6
+
+
+@pytest.mark.parametrize("m,my,nbytes", [((6, 3, 2), (4, 3, 2), 29184), ((24, 11, 146), (7, 4, 38), 444928),
+                                         ((4, 8, 8), (5, 9, 9), 83200), ((206, 282, 1), (53, 72, 1), 732672)],
+                         ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_workspace_sizes_of_longer_chunks_are_still_taken(m, my, nbytes):
+    """Sizes that were asked for before the split into short chunks: such a workspace gets long ones."""
+    lib = mfr.load()
+    grid = mfr.make_grid(GridSpec(m=m, h=(1.0, 1.0, 1.0), my=my, tau=0.1, rho=0.1, alpha=1.0))
+    ws = torch.empty(nbytes + 256, dtype=torch.uint8, device=DEV)
+    h = ctypes.c_void_p()
+    ptr = ws.data_ptr() + (-ws.data_ptr()) % 256
+    assert lib.mfr_create(ctypes.byref(grid), None, ctypes.c_void_p(ptr), nbytes, ctypes.byref(h)) == 0
+    lib.mfr_destroy(h)
