@@ -219,10 +219,12 @@ hipError_t launch_pcg_alpha_batch(const VecJobs& j, hipStream_t st) {
 // them hold the same alpha (beta) and the same verdict, and the first group of a
 // problem writes the scalars and the control state.  The kernels with one group per
 // problem that formed alpha and beta took 4.5 us each, plus their launch gaps, for
-// a few hundred additions.  Nothing that a group reads here is written by another
-// group of the same launch, except the active flag, which only ever turns the
-// remaining groups of a solve that has just stopped into no-ops: their vectors are
-// not used any more.
+// a few hundred additions.  Nothing that the update's groups read is written in its
+// launch: a breakdown it finds ends the solve in the step kernel, which sees it from
+// the stored p.q.  There the first group clears the active flag while others start,
+// so one thread reads the flag for its whole group: waves that each read it could
+// part, and those left would sum without the others' share.  A group that finds the
+// flag cleared has nothing to do: the solve is over and its p is not used any more.
 __device__ __forceinline__ double sum_parts(const double* __restrict__ parts, int n, double* sred, double* stot) {
   double a = 0.0, b = 0.0;
   int i = threadIdx.x;
@@ -237,8 +239,11 @@ __device__ __forceinline__ double sum_parts(const double* __restrict__ parts, in
   return *stot;
 }
 
-// alpha = r.z / p.q (a breakdown, p.q <= 0 or not finite, ends the problem without
-// the update); s += alpha p, r -= alpha q, z = M^-1 r; partials of r.r and r.z.
+// A breakdown: p.q <= 0 or not finite.
+__device__ __forceinline__ bool pq_ok(double pq) { return pq > 0.0 && isfinite(pq); }
+
+// alpha = r.z / p.q; s += alpha p, r -= alpha q, z = M^-1 r (none of these after a
+// breakdown); partials of r.r and r.z.
 __global__ __launch_bounds__(kVecBlock) void pcg_update_batch_kernel(const VecJobs J) {
   __shared__ double sred[kVecBlock / 64], stot;
   const int pr = find_job(J.prefix, J.n, blockIdx.x);
@@ -247,7 +252,7 @@ __global__ __launch_bounds__(kVecBlock) void pcg_update_batch_kernel(const VecJo
   const int lb = blockIdx.x - J.prefix[pr], nb = J.prefix[pr + 1] - J.prefix[pr];
   const double rz_old = ld_coherent(v.sc + SC_RZ);
   const double pq = sum_parts(v.red_pq, v.n_pq, sred, &stot);
-  const bool ok = pq > 0.0 && isfinite(pq);
+  const bool ok = pq_ok(pq);
   const double alpha_d = ok ? rz_old / pq : 0.0;
   if (lb == 0 && threadIdx.x == 0) {
     double* sc = v.sc;
@@ -255,11 +260,6 @@ __global__ __launch_bounds__(kVecBlock) void pcg_update_batch_kernel(const VecJo
     sc[SC_ALPHA] = alpha_d;
     sc[SC_RZOLD] = rz_old;
     v.state[ST_NEXT] = ld_coherent(v.state + ST_ITERS) + 1;
-    if (!ok) {
-      v.state[ST_FLAG] = 2;
-      v.state[ST_ACTIVE] = 0;
-      J.active_out[pr] = 0;
-    }
   }
   if (!ok) return;
   const float alpha = (float)alpha_d;
@@ -287,13 +287,25 @@ hipError_t launch_pcg_update_batch(const VecJobs& j, hipStream_t st) {
 }
 
 // |r|, beta = (r.z)_new / (r.z)_old and the convergence test; p = z + beta p unless
-// the solve has stopped.
+// the solve has stopped.  After a breakdown it only ends the solve.
 __global__ __launch_bounds__(kVecBlock) void pcg_step_batch_kernel(const VecJobs J) {
   __shared__ double sred[kVecBlock / 64], stot;
+  __shared__ int sgo;   // 0: stopped before this launch or already by it; 1: go on; 2: breakdown
   const int pr = find_job(J.prefix, J.n, blockIdx.x);
   const VecJob& v = J.jobs[pr];
-  if (!ld_coherent(v.state + ST_ACTIVE)) return;
+  if (threadIdx.x == 0) {
+    const double pq = ld_coherent(v.sc + SC_PQ);
+    sgo = !ld_coherent(v.state + ST_ACTIVE) ? 0 : pq_ok(pq) ? 1 : 2;
+  }
+  __syncthreads();
+  const int go = sgo;
   const int lb = blockIdx.x - J.prefix[pr], nb = J.prefix[pr + 1] - J.prefix[pr];
+  if (go == 2 && lb == 0 && threadIdx.x == 0) {
+    v.state[ST_FLAG] = 2;
+    v.state[ST_ACTIVE] = 0;
+    J.active_out[pr] = 0;
+  }
+  if (go != 1) return;
   const double rr = sum_parts(v.red, nb, sred, &stot);
   __syncthreads();
   const double rz = sum_parts(v.red + nb, nb, sred, &stot);
