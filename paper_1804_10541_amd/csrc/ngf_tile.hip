@@ -223,7 +223,6 @@ __device__ __forceinline__ void tile_body(const TileParams& P, const int bid, co
       const float* const V = &sV[d][0];
       const size_t o0 = (size_t)d * P.nbar + (size_t)(noz + kloc) * nxy + (size_t)noy * P.nx + nox;
       f32x4 acc[RT];
-      float fin = 0.f;   // stays 0 if every column's value is finite, else turns NaN
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
         const float* const row = V + min(rt * 16 + c16, BY - 1) * VP + quad;
@@ -242,48 +241,13 @@ __device__ __forceinline__ void tile_body(const TileParams& P, const int bid, co
             s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], b[j], s0, 0, 0, 0);
             s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j + 1], b[j + 1], s1, 0, 0, 0);
           }
-#pragma unroll
-          for (int j = 0; j < G; ++j) fin = fmaf(a[j], 0.f, fin);
         }
         acc[rt] = s0 + s1;
       }
-      // a zero weight must not carry an infinity or NaN of a far column to a node:
-      // such a plane is summed without the matrix cores, zero weights left out
-      const bool bad = __any(fin != 0.f);
-      if (bad) {
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-          acc[rt] = (f32x4){0.f, 0.f, 0.f, 0.f};
-#pragma clang loop unroll(disable)
-          for (int l = 0; l < BX; ++l) {
-            const float w = sWx[nt][l >> 2][16 * (l & 3) + c16];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              const float v = V[min(rt * 16 + 4 * quad + r, BY - 1) * VP + l];
-              acc[rt][r] = w != 0.f ? fmaf(w, v, acc[rt][r]) : acc[rt][r];
-            }
-          }
-        }
-      }
 #pragma clang loop unroll(disable)
       for (int mt = 0; mt * 16 < nyl; ++mt) {
-        f32x4 o = (f32x4){0.f, 0.f, 0.f, 0.f};
-        if (bad) {
-#pragma unroll
-          for (int rt = 0; rt < RT; ++rt)
-#pragma clang loop unroll(disable)
-            for (int q = 0; q < 4; ++q)
-#pragma unroll
-              for (int r = 0; r < 4; ++r) {
-                const float v = __shfl(acc[rt][r], 16 * q + c16, 64);   // row 16 rt + 4 q + r
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                  const float w = sWy[mt][4 * rt + r][16 * q + 4 * quad + k];
-                  o[k] = w != 0.f ? fmaf(w, v, o[k]) : o[k];
-                }
-              }
-        } else {
-          f32x4 o1 = (f32x4){0.f, 0.f, 0.f, 0.f};
+        f32x4 o = (f32x4){0.f, 0.f, 0.f, 0.f}, o1 = o;
+        {
           float a[4 * RT];
 #pragma unroll
           for (int r = 0; r < 4 * RT; ++r) a[r] = sWy[mt][r][lane];
@@ -293,6 +257,39 @@ __device__ __forceinline__ void tile_body(const TileParams& P, const int bid, co
             o1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[r + 1], acc[r >> 2][(r & 3) + 1], o1, 0, 0, 0);
           }
           o += o1;
+        }
+        // A zero weight must not carry an infinity or NaN of a far column or of a row's
+        // overflowing sum to a node.  Either is in every output of its columns then, and
+        // the plane is summed without the matrix cores, zero weights left out.
+        float fin = 0.f;   // stays 0 if every output is finite, else turns NaN
+#pragma unroll
+        for (int r = 0; r < 4; ++r) fin = fmaf(o[r], 0.f, fin);
+        if (__any(fin != 0.f)) {
+          o = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma clang loop unroll(disable)
+          for (int rt = 0; rt < RT; ++rt) {
+            f32x4 x = (f32x4){0.f, 0.f, 0.f, 0.f};   // sums over x, as acc
+#pragma clang loop unroll(disable)
+            for (int l = 0; l < BX; ++l) {
+              const float w = sWx[nt][l >> 2][16 * (l & 3) + c16];
+#pragma unroll
+              for (int r = 0; r < 4; ++r) {
+                const float v = V[min(rt * 16 + 4 * quad + r, BY - 1) * VP + l];
+                x[r] = w != 0.f ? fmaf(w, v, x[r]) : x[r];
+              }
+            }
+#pragma clang loop unroll(disable)
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+              for (int r = 0; r < 4; ++r) {
+                const float v = __shfl(x[r], 16 * q + c16, 64);   // row 16 rt + 4 q + r
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                  const float w = sWy[mt][4 * rt + r][16 * q + 4 * quad + k];
+                  o[k] = w != 0.f ? fmaf(w, v, o[k]) : o[k];
+                }
+              }
+          }
         }
         if (16 * nt + c16 < nxl) {
 #pragma unroll
