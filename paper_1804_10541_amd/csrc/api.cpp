@@ -514,6 +514,21 @@ static void set_node_groups(mfr_ctx* c) {
   c->np_groups = node_groups(c->geo.nbar);
 }
 
+// The voxel-tile kernel forms its rows without their factor 1 / (|grad T| |grad R|)
+// and applies it twice at the end; scaling the squared norms and r by a common factor
+// leaves its results the same.  With the power of two next to 1 / (tau rho) (exact, so
+// the bits stay, too) the values in between stay in range wherever the norms do:
+// unscaled they left it for images and edge parameters of about 1e-16 and below.
+// The exponent is bounded so that the scaled spacings stay far inside the range.
+static void scale_row_norms(TileParams& p) {
+  const float hi = std::max(p.hhx, std::max(p.hhy, p.hhz)), lo = std::min(p.hhx, std::min(p.hhy, p.hhz));
+  const double e = -0.5 * (std::log2((double)p.tau2) + std::log2((double)p.rho2));
+  int k = (int)std::lround(std::min(std::max(e, -80.0), 80.0));
+  if (k > 0) k = std::max(0, std::min(k, 100 - std::ilogb(hi)));
+  if (k < 0) k = std::min(0, std::max(k, -100 - std::ilogb(lo)));
+  for (float* f : {&p.hhx, &p.hhy, &p.hhz, &p.tau2, &p.rho2, &p.taurho}) *f = std::ldexp(*f, k);
+}
+
 // Context of a two-dimensional problem: tables, the tile kernel's parameters
 // (TileParams with mz = nz = 1), the node pass's view of the n[0] x n[1] node
 // grid as n[0] x 1 x n[1] (x tiles, one tile row, row chunks as z chunks; the
@@ -987,6 +1002,8 @@ mfr_status ctx_init(mfr_ctx* c, const mfr_grid* grid, void* stream, void* ws, si
   c->dtn.t.nzt = t.dgn.nzt;
   c->dtn.ntz = at<Range1>(c->ws, L.nntz);
   c->dtn.orgz = at<int>(c->ws, L.norgz);
+
+  if (!ssd) scale_row_norms(p);   // (the diagonal's parameters above keep the plain ones)
 
   c->sc = at<double>(c->ws, L.sc);
   c->red_tile = p.red;

@@ -79,7 +79,7 @@ struct TileParams {
   int PX, PY;             // padded template row / plane pitch (mT + 4)
   long long PXY;          // padded template plane size
   float ih2x, ih2y, ih2z; // 1 / h^2
-  float hhx, hhy, hhz;    // 1 / (2 h^2)
+  float hhx, hhy, hhz;    // 1 / (2 h^2) (voxel-tile kernel: times the power of two of tau2, rho2 and taurho)
   float ihTx, ihTy, ihTz; // 1 / hT
   int zcells2;            // every cell along z has two voxel planes or more (the image's first and last aside)
   float tau2, rho2, taurho;

@@ -559,7 +559,8 @@ __device__ __forceinline__ void tile_body(const TileParams& P, const int bid, co
         obj += 1.0 - ((double)r1 * (double)r1) / ((double)nT2 * (double)nR2);
       if constexpr (NEED_C) {
         // rows rho-hat(k) = q(k) / (|grad T| |grad R|): every product that leaves the
-        // stage holds two of them, so no square root is formed
+        // stage holds two of them, so no square root is formed (the host scales the
+        // squared norms, r1 and q by about 1 / (tau rho), which cancels)
         const float rT = rcp_norm(nT2), rR = rcp_norm(nR2);
         const float c2 = r1 * rT;
         const float qxm = P.hhx * fmaf(-c2, dTxm, dRxm), qxp = P.hhx * fmaf(-c2, dTxp, dRxp);
