@@ -261,17 +261,26 @@ static int pick_chunks(long long xy, int planes, int min_len, int max_len, int p
   return best;
 }
 
-// The least chunk length, from 4 planes on, with at most two chunks holding one
-// node plane, so that the partial slots of P^T along the march stay at two.
-static int min_chunk(const std::vector<Conv1>& c, int n) {
+// The least chunk length of a derived split: from 4 planes on the first with at most
+// `slots` chunks holding one node plane, because the node passes walk that many
+// partial slots, and at most 16 planes: longer chunks on deep cells leave the chip
+// idle for the sake of few node planes.  Three dimensions take two slots: gradient
+// and diagonal of 128x128x96 voxels, 65x65x2 nodes 59 and 86 us with chunks of 48
+// planes, 39 and 57 us with 16; four slots give 37 and 60 us on 65x65x5 nodes against
+// 38 and 55 us with two, and 87 and 195 against 87 and 163 us on 256x256x112 voxels,
+// 9x9x5 nodes.  Two dimensions take eight (a plane has few columns of groups to fill
+// the chip): 1024x1024 pixels, 33x33 nodes 32.1 and 47.9 us with two, 31.0 and 43.9
+// with eight, 35.8 and 57.4 with any number; 9x9 nodes 60 and 59 us in chunks of 16
+// rows, 84 and 92 us of 4.
+static int min_chunk(const std::vector<Conv1>& c, int n, int slots) {
   const std::vector<Range1> cols = node_cols(c, n);
   auto over = [&](int len) {
     for (const Range1& r : cols)
-      if (r.hi / len - r.lo / len > 1) return true;
+      if (r.hi / len - r.lo / len >= slots) return true;
     return false;
   };
   int len = 4;
-  while (len < (int)c.size() && over(len)) ++len;
+  while (len < std::min(16, (int)c.size()) && over(len)) ++len;
   return len;
 }
 
@@ -310,7 +319,7 @@ static Tiling make_tiling_plane(const Geo& g, const std::vector<Conv1>& cx, cons
     // Measured with the gradient: 4096 x 4096 in 90 chunks of 46 rows 78 us (121 of
     // 34, a round and a third: 96 us), 1024 x 1024 in chunks of 4 rows 16 us (of 16:
     // 23 us), 256 x 256 12 us (21 us)
-    chunks = pick_chunks(t.tiles_x, g.m[1], 4, kMaxChunk, 6, 4.0, 0.52);
+    chunks = pick_chunks(t.tiles_x, g.m[1], min_chunk(cy, g.n[1], 8), kMaxChunk, 6, 4.0, 0.52);
   }
   int clen = (g.m[1] + chunks - 1) / chunks;
   if (cfg.chunk_len > 0) clen = cfg.chunk_len;
@@ -387,7 +396,7 @@ Tiling make_tiling(const Geo& g, const std::vector<Conv1>& cx, const std::vector
   t.tiles_x = (g.m[0] + TX - 1) / TX;
   t.tiles_y = (g.m[1] + TY - 1) / TY;
   const int xy = t.tiles_x * t.tiles_y;
-  const int minc = min_chunk(cz, g.n[2]);
+  const int minc = min_chunk(cz, g.n[2], 2);
   int chunks;
   if (cfg.target_groups > 0 || compact) {   // a given number of groups, chunks of at least 16 planes
     const int target = cfg.target_groups > 0 ? cfg.target_groups : 2048;
