@@ -258,6 +258,16 @@ __device__ __forceinline__ void tile_body(const TileParams& P, const int bid, co
           }
           o += o1;
         }
+        auto store = [&]() {
+          if (16 * nt + c16 < nxl) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const int fr = 16 * mt + 4 * quad + r;
+              if (fr < nyl) part[o0 + (size_t)fr * P.nx + 16 * nt + c16] = o[r];
+            }
+          }
+        };
+        store();
         // A zero weight must not carry an infinity or NaN of a far column or of a row's
         // overflowing sum to a node.  Either is in every output of its columns then, and
         // the plane is summed without the matrix cores, zero weights left out.
@@ -290,13 +300,7 @@ __device__ __forceinline__ void tile_body(const TileParams& P, const int bid, co
                 }
               }
           }
-        }
-        if (16 * nt + c16 < nxl) {
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int fr = 16 * mt + 4 * quad + r;
-            if (fr < nyl) part[o0 + (size_t)fr * P.nx + 16 * nt + c16] = o[r];
-          }
+          store();
         }
       }
     }
