@@ -460,7 +460,7 @@ static int node_groups(size_t nbar) {
   return (int)((sets + per - 1) / per);
 }
 
-Layout make_layout(const Geo& g, const Tiling& t) {
+Layout make_layout(const Geo& g, const Tiling& t, bool product_only) {
   Layout L;
   size_t o = 0;
   auto take = [&](size_t bytes) {
@@ -498,13 +498,14 @@ Layout make_layout(const Geo& g, const Tiling& t) {
   // (one diagonal at a time on the context's stream: both tilings share the blocks)
   L.nntz = take(t.dgn.on ? sizeof(Range1) * g.n[2] : 0);
   L.norgz = take(t.dgn.on ? sizeof(int) * t.dgn.chunks : 0);
-  L.dpart = take(sizeof(float) * std::max(dg.floats(), t.dgn.floats()));
+  L.dpart = take(product_only ? 0 : sizeof(float) * std::max(dg.floats(), t.dgn.floats()));
   L.red_tile = take(sizeof(double) * (size_t)t.grid());
   // node-pass partials (one per group) and those of the other vector kernels
   L.red_node = take(sizeof(double) * std::max(node_groups(g.nbar), 2 * 1024));
-  L.red_vec = take(sizeof(double) * 2 * std::min<size_t>((nc * g.nbar + kVecBlock - 1) / kVecBlock, 1024));   // of the CG vector kernels (two per group)
+  // of the CG vector kernels (two per group)
+  L.red_vec = take(sizeof(double) * 2 * std::min<size_t>((nc * g.nbar + kVecBlock - 1) / kVecBlock, 1024));
   L.sc = take(sizeof(double) * SC_COUNT);
-  L.vec = take(sizeof(float) * nc * g.nbar * 8);   // PCG r z p q diag; GN rhs, trial, direction
+  L.vec = take(product_only ? 0 : sizeof(float) * nc * g.nbar * 8);   // PCG r z p q diag; GN rhs, trial, direction
   L.div = take(sizeof(float) * g.nbar);           // elastic: divergence per cell of the nodal grid
   L.ctrl = take(sizeof(int) * (2 + ST_COUNT));    // device-steered CG: active flag, state; line-search flag
   L.total = o;
@@ -548,10 +549,10 @@ static mfr_status ctx_init_plane(mfr_ctx* c, void* stream, void* ws, size_t ws_b
   auto cx = conv_table(g.m[0], g.n[0]);
   auto cy = conv_table(g.m[1], g.n[1]);
   c->tiling = make_tiling(g, cx, cy, cy);
-  c->lay = make_layout(g, c->tiling);
+  c->lay = make_layout(g, c->tiling, c->product_only);
   if (ws_bytes < c->lay.total) {   // longer chunks, fewer partials
     c->tiling = make_tiling(g, cx, cy, cy, true);
-    c->lay = make_layout(g, c->tiling);
+    c->lay = make_layout(g, c->tiling, c->product_only);
   }
   if (!ws) return fail(MFR_EINVAL, "workspace is NULL");
   if (reinterpret_cast<uintptr_t>(ws) % 256 != 0) return fail(MFR_EINVAL, "workspace must be 256-byte aligned");
@@ -757,10 +758,10 @@ mfr_status ctx_init(mfr_ctx* c, const mfr_grid* grid, void* stream, void* ws, si
   auto cz = conv_table(g.m[2], g.n[2]);
   c->tiling = make_tiling(g, cx, cy, cz);
   if (!valid_shape(c->tiling.shape)) return fail(MFR_EINVAL, "unsupported tile shape %dx%d", c->tiling.shape.bx, c->tiling.shape.by);
-  c->lay = make_layout(g, c->tiling);
+  c->lay = make_layout(g, c->tiling, c->product_only);
   if (ws_bytes < c->lay.total) {   // the longer chunks of the compact tiling need fewer partial blocks
     c->tiling = make_tiling(g, cx, cy, cz, true);
-    c->lay = make_layout(g, c->tiling);
+    c->lay = make_layout(g, c->tiling, c->product_only);
   }
   if (!ws) return fail(MFR_EINVAL, "workspace is NULL");
   if (reinterpret_cast<uintptr_t>(ws) % 256 != 0) return fail(MFR_EINVAL, "workspace must be 256-byte aligned");

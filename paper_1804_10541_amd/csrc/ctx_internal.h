@@ -111,7 +111,8 @@ struct Layout {
   size_t total;
 };
 
-Layout make_layout(const Geo& g, const Tiling& t);
+// product_only: without the node vectors and the diagonal's blocks.
+Layout make_layout(const Geo& g, const Tiling& t, bool product_only = false);
 
 template <class T>
 T* at(char* base, size_t off) {
@@ -139,6 +140,8 @@ struct mfr_ctx {
   mfr::Layout lay;
   hipStream_t stream;
   char* ws;
+  // Set before ctx_init: no calls but mfr_set_images and the Hessian product follow.
+  bool product_only = false;
   // Results that a synchronous call returns, written by the device itself (pinned;
   // null: copied instead).  The capturable entry points never touch it: a graph may
   // outlive the context.

@@ -70,6 +70,10 @@ mfr_status mfr_hess_vec_noalloc(const mfr_grid* grid, void* hip_stream, const fl
   // run.  Every scratch entry the kernels read is written earlier in the same
   // call, so nothing needs clearing between calls.
   mfr_ctx c{};
+  // Room for the split of a full workspace (whose bits the product promises) where the
+  // array holds the whole context in longer chunks only: what a product does not use
+  // is left out, and that is more than the shorter chunks add.
+  c.product_only = true;
   MFR_TRY(ctx_init(&c, grid, hip_stream, ws, kScratchBytes));
   MFR_TRY(mfr_set_images(&c, R, T));
   return enqueue_hess_vec(&c, u, p, q);
