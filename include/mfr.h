@@ -178,7 +178,11 @@ mfr_status mfr_hess_vec_noalloc(const mfr_grid* grid, void* hip_stream, const fl
 
 /* diag = diag(H + alpha nabla^2 S) at u, exactly (the Jacobi preconditioner
  * of the conjugate-gradient solve; the paper leaves CG unpreconditioned).
- * Entries may be 0 when alpha = 0.  Asynchronous. */
+ * Entries may be 0 when alpha = 0.  While a learned preconditioner is bound to
+ * the context the sums are formed in that one's fixed order (the diagonal of
+ * mfr_pc_apply to the bit): other last bits, and slower where cells have two
+ * voxels or more (512x512x128 voxels, 129x129x33 nodes 890 against 500 us).
+ * Asynchronous. */
 mfr_status mfr_jacobi_diag(mfr_ctx* ctx, const float* u, float* diag);
 
 typedef struct {
@@ -461,7 +465,9 @@ void mfr_pc_destroy(mfr_pc* pc);
 /* Rebind to another context (another grid size; the network parameters and
  * optimiser state are kept).  The workspace must be large enough for that
  * context's grid (MFR_ENOMEM otherwise).  Detaches the preconditioner from its
- * previous context. */
+ * previous context.  A bound preconditioner changes the order of the sums of
+ * mfr_jacobi_diag on its context (see there) and nothing else of it: solves and
+ * steps with precond 0 or 1 keep their bits. */
 mfr_status mfr_pc_bind(mfr_pc* pc, mfr_ctx* ctx);
 /* Copy MFR_PC_PARAMS floats from / to host memory (synchronous). */
 mfr_status mfr_pc_set_params(mfr_pc* pc, const float* params);

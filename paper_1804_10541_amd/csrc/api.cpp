@@ -1061,23 +1061,22 @@ hipEvent_t prof_event(mfr_ctx* c) {
   return e;
 }
 
-hipError_t enqueue_diag(mfr_ctx* c, const float* u, float* diag) {
+hipError_t enqueue_diag(mfr_ctx* c, const float* u, float* diag, bool network) {
   if (c->geo.dim == 2)
     return c->tiling.dg.on ? launch_diag_tile(c->dtp, u, diag, c->stream) : launch_plane_jacobi(c->dp, u, diag, c->stream);
-  // With a learned preconditioner bound, one order of summation whatever split and
-  // kernel the diagonal takes otherwise: its network rounds the diagonal to 16 bits, so
-  // the last bit of a sum can change an activation by 2^-9 (outputs 2e-3 of their
-  // size apart with another z split alone, on half of the inputs tried).  Every caller
-  // of such a context gets the same bits (a network of zeros is exactly Jacobi).
-  if (c->tiling.dg.on) return launch_diag_tile(c->bound_pcs.empty() ? c->dtp : c->dtn, u, diag, c->stream);
+  // For the learned preconditioner, one order of summation whatever split and kernel
+  // the diagonal takes otherwise: its network rounds the diagonal to 16 bits, so the
+  // last bit of a sum can change an activation by 2^-9 (outputs 2e-3 of their size
+  // apart with another z split alone, on half of the inputs tried).
+  if (c->tiling.dg.on) return launch_diag_tile(network ? c->dtn : c->dtp, u, diag, c->stream);
   if (c->jac_tiled) return launch_jacobi_tile(c->jp, u, diag, c->stream);
   return launch_jacobi_diag(c->dp, u, diag, c->stream);
 }
 
 // The Jacobi preconditioner of a CG solve: the exact diagonal with zero entries
 // replaced by 1.
-hipError_t enqueue_pcg_diag(mfr_ctx* c, const float* u, float* diag) {
-  hipError_t e = enqueue_diag(c, u, diag);
+hipError_t enqueue_pcg_diag(mfr_ctx* c, const float* u, float* diag, bool network) {
+  hipError_t e = enqueue_diag(c, u, diag, network);
   if (e != hipSuccess) return e;
   return launch_safe_diag((int)(c->geo.nc() * c->geo.nbar), diag, c->stream);
 }
@@ -1269,7 +1268,7 @@ mfr_status pcg_run_flexible(mfr_ctx* c, const float* u, const float* b, float* s
   float* diag = c->vec[4];
   int* active = c->ctrl;
   int* state = c->ctrl + 1;
-  HIP_TRY(timed(c, 3, [&] { return enqueue_pcg_diag(c, u, diag); }));
+  HIP_TRY(timed(c, 3, [&] { return enqueue_pcg_diag(c, u, diag, true); }));
   VecJobs V{};
   V.n = 1;
   V.prefix[0] = 0;
@@ -1563,7 +1562,9 @@ mfr_status mfr_jacobi_diag(mfr_ctx* c, const float* u, float* diag) {
   MFR_TRY(need_images(c));
   MFR_TRY(check_ptr(u, "u"));
   MFR_TRY(check_ptr(diag, "diag"));
-  HIP_TRY(timed(c, 3, [&] { return enqueue_diag(c, u, diag); }));   // the exact diagonal
+  // the exact diagonal; that of the learned preconditioner where one is bound, whose
+  // direction with a network of zeros is r / diag to the bit
+  HIP_TRY(timed(c, 3, [&] { return enqueue_diag(c, u, diag, !c->bound_pcs.empty()); }));
   return MFR_OK;
 }
 

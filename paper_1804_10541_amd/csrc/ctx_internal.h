@@ -219,8 +219,9 @@ hipError_t timed(mfr_ctx* c, int slot, F&& launch) {
   return hipSuccess;
 }
 
-hipError_t enqueue_diag(mfr_ctx* c, const float* u, float* diag);
-hipError_t enqueue_pcg_diag(mfr_ctx* c, const float* u, float* diag);   // zero entries -> 1
+// network: in the learned preconditioner's order of summation
+hipError_t enqueue_diag(mfr_ctx* c, const float* u, float* diag, bool network);
+hipError_t enqueue_pcg_diag(mfr_ctx* c, const float* u, float* diag, bool network = false);   // zero entries -> 1
 int node_blocks(const mfr_ctx* c);   // work-groups of a node pass
 int node_parts(const mfr_ctx* c);    // float64 partials of a gradient / Hv node pass (one per group)
 mfr_status check_ptr(const void* p, const char* name);

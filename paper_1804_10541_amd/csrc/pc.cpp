@@ -510,7 +510,7 @@ mfr_status mfr_pc_apply(mfr_pc* pc, const float* u, const float* r, float* z) {
   MFR_TRY(check_ptr(r, "r"));
   MFR_TRY(check_ptr(z, "z"));
   if (z == r || z == u) return fail(MFR_EINVAL, "z must not alias u or r");
-  HIP_TRY(enqueue_diag(pc->c, u, pc->diag));
+  HIP_TRY(enqueue_diag(pc->c, u, pc->diag, true));
   MFR_TRY(refresh_gR(pc));
   return pc_forward(pc, r, pc->diag, z, false, nullptr, nullptr, nullptr, false, true);
 }
@@ -532,7 +532,7 @@ mfr_status mfr_pc_train_system(mfr_pc* pc, const float* u, const float* b, const
   float* z = c->vec[1];
   float* p = c->vec[2];
   float* q = c->vec[3];
-  HIP_TRY(enqueue_diag(c, u, pc->diag));
+  HIP_TRY(enqueue_diag(c, u, pc->diag, true));
   MFR_TRY(pc_begin_solve(pc, pc->diag));
   HIP_TRY(launch_pcg_init(n3, b, pc->diag, pc->s, r, z, p, c->red_node, vb, st));
   HIP_TRY(launch_pcg_init_finish(c->red_node, vb, c->sc, st));
