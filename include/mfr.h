@@ -109,7 +109,8 @@ const char* mfr_last_error(void);
  * reduction partials, lookup tables, the template copy with a zero border
  * that realises its Dirichlet extension, and the six node vectors of PCG).
  * Where a smaller workspace holds the same problem split into fewer, longer
- * chunks, a context accepts it as well and runs slower. */
+ * chunks, a context accepts it as well, runs slower and may differ in the last
+ * bits (another order of summation). */
 mfr_status mfr_workspace_size(const mfr_grid* grid, size_t* bytes);
 
 /* Create a context bound to `hip_stream` (a hipStream_t; NULL = default
@@ -163,11 +164,12 @@ mfr_status mfr_gradient_async(mfr_ctx* ctx, const float* u, double* J, float* g)
  * with the workspace taken from a fixed device array of
  * MFR_NOALLOC_SCRATCH_BYTES bytes that the library holds on every GPU it runs
  * on until the process ends.  Same kernels, same result bit for bit as
- * mfr_create + mfr_set_images + mfr_hess_vec with the same tile configuration.
+ * mfr_create (with mfr_workspace_size bytes) + mfr_set_images + mfr_hess_vec
+ * with the same tile configuration.
  * Allocates no device memory and needs no context or workspace.  All pointers
  * are device pointers on the current device; work is enqueued on hip_stream,
- * which must belong to that device.  Returns MFR_ENOMEM if the problem's
- * workspace (mfr_workspace_size) exceeds the array.  Every call on one GPU
+ * which must belong to that device.  Returns MFR_ENOMEM if the array is
+ * smaller than any workspace that a context of the problem accepts.  Every call on one GPU
  * uses the same array: calls that overlap in time (other streams, other host
  * threads) race and must not be issued; calls in order on one stream are
  * safe, each one rewriting what it reads.  Asynchronous after the table
@@ -391,11 +393,13 @@ mfr_status mfr_lbfgs(mfr_ctx* ctx, float* u, const mfr_lbfgs_opts* opts, void* w
  * Up to MFR_MAX_BATCH image pairs of different sizes advance together: every
  * phase (voxel-tile kernels, node passes, sums, CG vector updates) is one
  * launch for all pairs (the voxel-tile kernels over the joined tile list of all
- * pairs).  The CG iteration is steered on the device (per-pair convergence flags), so a block of iterations is
- * captured once into a HIP graph and replayed.  Results equal running each pair
- * alone through mfr_register_multilevel, bit for bit.  This is an extension of
- * the paper's single-pair method (Sec. 2.3) for throughput; it is not in the
- * paper. */
+ * pairs).  The CG iteration is steered on the device (per-pair convergence
+ * flags), so a block of iterations is captured once into a HIP graph and
+ * replayed.  Results equal running each pair alone through
+ * mfr_register_multilevel, bit for bit, where both have workspaces of the sizes
+ * that their queries return (a smaller one may take longer chunks, whose sums
+ * have another order).  This is an extension of the paper's single-pair method
+ * (Sec. 2.3) for throughput; it is not in the paper. */
 #define MFR_MAX_BATCH 12
 
 typedef struct mfr_batch mfr_batch;   /* opaque host-side batch context */
@@ -520,8 +524,8 @@ mfr_status mfr_cnn_conv_bwd_weight(int32_t nx, int32_t ny, int32_t nz, const uin
  * Shape of the voxel-tile work-groups (bx x by threads: 32x16, 64x8, 32x32 or
  * 64x16), the number of z planes per group (chunk_len; 0 = derived) and the
  * number of work-groups the derived split aims for (target_groups; 0 = chosen
- * from the grid by an estimate of the rounds of work-groups), for contexts and batches created afterwards in
- * this process.  Returns MFR_EINVAL for an unsupported shape or a negative
+ * from the grid by an estimate of the rounds of work-groups), for contexts and
+ * batches created afterwards in this process.  Returns MFR_EINVAL for an unsupported shape or a negative
  * count.  The tile autotuner sets it from measured timings. */
 typedef struct {
   int32_t bx, by, chunk_len, target_groups;
