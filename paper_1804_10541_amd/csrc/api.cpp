@@ -316,9 +316,9 @@ static Tiling make_tiling_plane(const Geo& g, const std::vector<Conv1>& cx, cons
     chunks = std::min(chunks, std::max(1, g.m[1] / 16));
   } else {
     // six groups per CU (registers), one alone 0.52 of their time, lead-in 4 rows.
-    // Measured with the gradient: 4096 x 4096 in 90 chunks of 46 rows 78 us (121 of
-    // 34, a round and a third: 96 us), 1024 x 1024 in chunks of 4 rows 16 us (of 16:
-    // 23 us), 256 x 256 12 us (21 us)
+    // The gradient's tile kernel (event times): 4096 x 4096 pixels, 2049 x 2049 nodes
+    // in 90 chunks of 46 rows 85-91 us (121 of 34, a round and a third: 97 us),
+    // 1024 x 1024 in chunks of 4 rows 16 us (of 16: 22 us), 256 x 256 11 us (21 us)
     chunks = pick_chunks(t.tiles_x, g.m[1], min_chunk(cy, g.n[1], 8), kMaxChunk, 6, 4.0, 0.52);
   }
   int clen = (g.m[1] + chunks - 1) / chunks;

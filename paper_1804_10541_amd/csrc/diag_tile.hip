@@ -552,12 +552,12 @@ __device__ __forceinline__ NodeCols node_columns(const Conv1* c, int B, int firs
 // that a row reaches: a third of the operations and one barrier per plane.
 // Everything that a thread needs rarely is read from LDS, so that 128 registers
 // (two groups per CU) hold the rest: a spilled value would wait for the template
-// loads in flight (six of them cost 636 -> 524 us below).
+// loads in flight (a form with six of them took a fifth longer).
 //
-// Bound by vector-instruction issue (about 340 per row plane and wave).  The
-// diagonal with its node pass, gather -> march (NGF; SSD): 512x512x128 voxels,
-// 129x129x33 nodes 894 -> 510 us (SSD 480 -> 202), 257x257x65 nodes 1290 -> 740 us,
-// 128x128x96, 65x65x49 nodes 97 -> 65 us.
+// Bound by vector-instruction issue (about 340 per row plane and wave).  A call of the
+// diagonal with its node pass, gather -> march with each one's own z split:
+// 512x512x128 voxels, 129x129x33 nodes 945 -> 495 us (SSD 518 -> 186), 257x257x65
+// nodes 1359 -> 712 us, 128x128x96, 65x65x49 nodes 136 -> 64 us.
 template <bool SSD, bool SCALED>
 __global__ __launch_bounds__(kDiagBX* kDiagBY) __attribute__((amdgpu_waves_per_eu(4))) void diag_march_kernel(
     const DiagTileParams D, const float* __restrict__ u) {
@@ -680,21 +680,21 @@ __global__ __launch_bounds__(kDiagBX* kDiagBY) __attribute__((amdgpu_waves_per_e
     const bool own = fx >= 1 && fx < BX - 1 && fy >= 1 && fy < BY - 1;
     const float wx1 = S.sAx[fx].f, wy1 = S.sAy[fy].f;
     if (own) {
-     if constexpr (SSD) {
+      if constexpr (SSD) {
 #pragma unroll
-      for (int d = 0; d < 3; ++d) S.sB[d][o] = lo[d][0];
-     } else {
+        for (int d = 0; d < 3; ++d) S.sB[d][o] = lo[d][0];
+      } else {
 #pragma unroll
-      for (int d = 0; d < 3; ++d) {
+        for (int d = 0; d < 3; ++d) {
 #pragma unroll
-        for (int a = 0; a < 4; ++a) {
-          const float W = SCALED ? column_weight(a, wx1, wy1) : 1.0f;
-          S.sB[4 * d + a][o] = W * W * lo[d][a];
+          for (int a = 0; a < 4; ++a) {
+            const float W = SCALED ? column_weight(a, wx1, wy1) : 1.0f;
+            S.sB[4 * d + a][o] = W * W * lo[d][a];
+          }
+          S.sB[12 + d][o] = exl[d];
+          S.sB[15 + d][o] = eyl[d];
         }
-        S.sB[12 + d][o] = exl[d];
-        S.sB[15 + d][o] = eyl[d];
       }
-     }
     }
     __syncthreads();
     // over the columns of each node, per own row inside the image

@@ -392,11 +392,13 @@ hipError_t launch_h0_tables(const H0Tables& t, const double hy[3], hipStream_t s
 // x = H_0^{-1} v.  ta, tb: scratch node vectors; x may alias v.
 // Five passes over the vector (z, y, x there and back, y, z), each read and written
 // once, against seven with a float32 product per axis and direction on the vector
-// units and the division apart.  Kernel time at 129x129x225 nodes, three components,
-// before -> now: z 175 + 175 -> 64 + 59 us, y 175 + 175 -> 42 + 40 us, x with the
-// division 138 + 36 + 138 -> 85 us; tables: seven copies from the host -> 4.8 us.
+// units and the division apart.  A call at 129x129x225 nodes, three components 1024 ->
+// 290 us; its kernels in a trace (which runs them a little slower): z 175 + 175 -> 65 +
+// 60 us, y 175 + 175 -> 42 + 40 us, x with the division 138 + 36 + 138 -> 87 us; tables:
+// seven copies from the host -> 5 us.
 // An x axis of more than 2 kH0Half nodes, whose 64 lines do not fit the registers,
-// takes the whole matrices and the division apart.
+// takes the whole matrices and the division apart: 257x33x33 nodes 205 -> 128 us (256:
+// 201 -> 69 us), 513x129x65 nodes 1423 -> 1010 us.
 hipError_t launch_h0_solve(const H0Tables& t, const float* v, float* x, float* ta, float* tb, float c2, float c1,
                            float gamma, hipStream_t st) {
   const int nx = t.n[0], ny = t.n[1], nz = t.n[2], nc = t.nc;

@@ -667,8 +667,8 @@ __device__ __forceinline__ void tile_body(const TileParams& P, const int bid, co
 // 1879 -> 1800 us, ten pairs 1825 -> 1765 us (8-byte loads of node pairs instead: 2075
 // us; the template's corner pairs as 4-byte loads: 1947 us).
 template <int BX, int BY, int MODE, bool SSD>
-__global__ __launch_bounds__(BX* BY) __attribute__((amdgpu_waves_per_eu(4))) void ngf_tile_kernel(const TileParams P, const float* __restrict__ u,
-                                                          const float* __restrict__ pv) {
+__global__ __launch_bounds__(BX* BY) __attribute__((amdgpu_waves_per_eu(4))) void ngf_tile_kernel(
+    const TileParams P, const float* __restrict__ u, const float* __restrict__ pv) {
   if (P.live && !ld_coherent(P.live)) return;   // a device-steered solve has stopped
   __shared__ TileSmem<BX, BY, MODE, SSD> S;
   tile_body<BX, BY, MODE, SSD>(P, xcd_block_id(), u, pv, S);

@@ -256,9 +256,9 @@ mfr_status pc_begin_solve(mfr_pc* pc, const float* diag) {
 
 // z = r / diag + rms(r / diag) * CNN(features)[0..2].  scales_ready: the RMS of
 // r and r/diag are already in the scalars (the flexible-CG update computes them).
-// diag_scale: the RMS of the diagonal is formed with them (one launch of sums and one
-// that finishes them instead of two each: 189 -> 176 us with the node sums of the diagonal for an application at 65x65x49
-// nodes), where pc_begin_solve has not.
+// diag_scale: the RMS of the diagonal is formed with them, where pc_begin_solve has
+// not (one launch of sums and one that finishes them instead of two each: with the
+// faster node sums of the diagonal 189 -> 176 us for an application at 65x65x49 nodes).
 // zred: the final layer also leaves per-group partials of z.r and z.rprev there.
 mfr_status pc_forward(mfr_pc* pc, const float* r, const float* diag, float* z, bool scales_ready,
                       const float* rprev, double* zred, const int* live, bool keep_input, bool diag_scale) {
