@@ -4,8 +4,17 @@ node plane: against the float64 oracle, float32 sums of up to a thousand terms p
 import pytest
 
 from gpu_cases import blob_case, gpu_eval, oracle_eval, rel_l2
+from paper_1804_10541_amd import mfr
 
 pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def derived_split():   # (another test's tile configuration may be in force)
+    old = mfr.get_tile_config()
+    mfr.set_tile_config(32, 16, 0, 0)
+    yield
+    mfr.set_tile_config(**old)
 
 
 @pytest.mark.parametrize("m,my", [((33, 20, 70), (9, 6, 2)), ((20, 17, 64), (5, 5, 3)), ((24, 31, 97), (4, 9, 4))],

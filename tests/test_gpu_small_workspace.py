@@ -13,6 +13,14 @@ from test_gpu_plane import plane_case
 pytestmark = pytest.mark.gpu
 
 
+@pytest.fixture(autouse=True)
+def derived_split():   # (another test's tile configuration may be in force)
+    old = mfr.get_tile_config()
+    mfr.set_tile_config(32, 16, 0, 0)
+    yield
+    mfr.set_tile_config(**old)
+
+
 @pytest.mark.parametrize("m,my", [((24, 11, 146), (7, 4, 38)), ((64, 64, 24), (33, 33, 13)), ((33, 20, 70), (17, 11, 36)),
                                   ((206, 282, 1), (53, 72, 1)), ((300, 60, 1), (76, 31, 1))],
                          ids=lambda v: "x".join(map(str, v)))

@@ -10,6 +10,14 @@ from paper_1804_10541_amd import mfr
 pytestmark = pytest.mark.gpu
 
 
+@pytest.fixture(autouse=True)
+def derived_split():   # (another test's tile configuration may be in force)
+    old = mfr.get_tile_config()
+    mfr.set_tile_config(32, 16, 0, 0)
+    yield
+    mfr.set_tile_config(**old)
+
+
 @pytest.mark.parametrize("m,my", [((78, 208, 89), (79, 36, 90)), ((241, 73, 59), (62, 74, 60))],
                          ids=lambda v: "x".join(map(str, v)))
 def test_product_equals_that_of_a_full_context(m, my):
